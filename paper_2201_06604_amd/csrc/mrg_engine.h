@@ -1,13 +1,12 @@
 // mrg_engine.h -- the exact generator steps on gfx950 (device code, included
 // by the kernel sources).  MRG32k3a in two interchangeable arithmetic forms:
 //
-//   IntEngine  32x32->64 multiply-adds, reduced with 2^32 = c (mod 2^32 - c)
-//   F64Engine  the same integers held exactly in fp64: every product is below
-//              2^53 and each remainder p - q*m is one exact FMA
+//   IntEngine    32x32->64 multiply-adds, reduced with 2^32 = c (mod 2^32 - c)
+//   F64EngineOf  the same integers held exactly in fp64: every product is below
+//                2^53 and each remainder p - q*m is one exact FMA
 //
-// Both give identical integers z in [1, m1].  MRG31k3p (Engine31) uses 32-bit
-// rotations for its power-of-two multipliers modulo the Mersenne prime p1 and
-// one 64-bit fold modulo p2.
+// Both give identical integers z in [1, m1].  MRG31k3p runs in the fp64 form
+// only.
 //
 // Every engine keeps each component as a ring of three registers holding
 // (x[n-3], x[n-2], x[n-1]); a step overwrites x[n-3] with x[n], so a 3-step
@@ -43,6 +42,7 @@ __device__ __forceinline__ uint32_t fold_m2(uint64_t p) {
 }
 
 struct IntEngine {
+    struct Regs {};  // its constants are literals
     uint32_t a0, a1, a2, b0, b1, b2;  // (x1[n-3], x1[n-2], x1[n-1]), (x2[...])
 
     __device__ __forceinline__ void load(const uint32_t x[6]) {
@@ -65,67 +65,12 @@ struct IntEngine {
     // Phase-P step of a 3-step cycle: the ring of registers rotates by naming,
     // so no moves are needed.
     template <int P>
-    __device__ __forceinline__ uint32_t step() {
+    __device__ __forceinline__ uint32_t step(const Regs&) {
         if (P == 0) return kernel(a0, a1, b0, b2);
         if (P == 1) return kernel(a1, a2, b1, b0);
         return kernel(a2, a0, b2, b1);
     }
-    __device__ __forceinline__ uint32_t step_rot() {
-        uint32_t z = kernel(a0, a1, b0, b2);
-        uint32_t t = a0; a0 = a1; a1 = a2; a2 = t;
-        t = b0; b0 = b1; b1 = b2; b2 = t;
-        return z;
-    }
-};
-
-// ------------------------------------------------------- MRG31k3p engine
-// 2^k x mod (2^31 - 1) for x < 2^31 - 1: a 31-bit rotation (2^31 = 1).  The
-// result is below 2^31 - 1 because x is.
-template <int K>
-__device__ __forceinline__ uint32_t rot31(uint32_t x) {
-    return ((x << K) & kP1) | (x >> (31 - K));
-}
-
-// a + b mod m for a, b < m < 2^31: one conditional subtraction (min picks the
-// reduced value; a + b - m wraps above it when a + b < m).
-__device__ __forceinline__ uint32_t add_mod31(uint32_t a, uint32_t b, uint32_t m) {
-    const uint32_t s = a + b;
-    return min(s, s - m);
-}
-
-struct Engine31 {
-    uint32_t a0, a1, a2, b0, b1, b2;  // (x1[n-3], x1[n-2], x1[n-1]), (x2[...])
-
-    // The stored state is newest-first: (x1[n-1], x1[n-2], x1[n-3], x2[...]).
-    __device__ __forceinline__ void load(const uint32_t x[6]) {
-        a0 = x[2]; a1 = x[1]; a2 = x[0]; b0 = x[5]; b1 = x[4]; b2 = x[3];
-    }
-    __device__ __forceinline__ void save(uint32_t x[6]) const {
-        x[0] = a2; x[1] = a1; x[2] = a0; x[3] = b2; x[4] = b1; x[5] = b0;
-    }
-    // o1 = x1[n-3] (becomes x1[n]), m2_1 = x1[n-2], o2 = x2[n-3] (becomes
-    // x2[n]), n1_2 = x2[n-1]; returns z in [1, p1].
-    static __device__ __forceinline__ uint32_t kernel(uint32_t& o1, uint32_t m2_1, uint32_t& o2,
-                                                      uint32_t n1_2) {
-        // x1[n] = 2^22 x1[n-2] + 2^7 x1[n-3] + x1[n-3]  (mod p1)
-        const uint32_t x1 = add_mod31(add_mod31(rot31<22>(m2_1), rot31<7>(o1), kP1), o1, kP1);
-        // x2[n] = 2^15 (x2[n-1] + x2[n-3]) + x2[n-3]  (mod p2), p < 2^47 + 2^31
-        const uint64_t p = (static_cast<uint64_t>(n1_2 + o2) << 15) + o2;
-        const uint32_t h = static_cast<uint32_t>(p >> 31), l = static_cast<uint32_t>(p) & 0x7fffffffu;
-        const uint32_t t = __umul24(h, kQ2) + l;                      // h < 2^17: t < 2^32
-        const uint32_t t2 = (t >> 31) * kQ2 + (t & 0x7fffffffu);      // < 2^31 + q2 < 2 p2
-        const uint32_t x2 = min(t2, t2 - kP2);
-        o1 = x1;
-        o2 = x2;
-        return x1 > x2 ? x1 - x2 : x1 - x2 + kP1;
-    }
-    template <int P>
-    __device__ __forceinline__ uint32_t step() {
-        if (P == 0) return kernel(a0, a1, b0, b2);
-        if (P == 1) return kernel(a1, a2, b1, b0);
-        return kernel(a2, a0, b2, b1);
-    }
-    __device__ __forceinline__ uint32_t step_rot() {
+    __device__ __forceinline__ uint32_t step_rot(const Regs&) {
         uint32_t z = kernel(a0, a1, b0, b2);
         uint32_t t = a0; a0 = a1; a1 = a2; a2 = t;
         t = b0; b0 = b1; b1 = b2; b2 = t;
@@ -134,64 +79,122 @@ struct Engine31 {
 };
 
 // ------------------------------------------------------------ fp64 engine
-constexpr double kM1d = static_cast<double>(kM1);
-constexpr double kM2d = static_cast<double>(kM2);
-constexpr double kInvM1 = 1.0 / kM1d;
-constexpr double kInvM2 = 1.0 / kM2d;
+// Constants of generator G in fp64.  Both components are carried less half of
+// the second modulus, h = (m2 - 1)/2, so a recurrence
+//   x[n] = (p x[n-i] + q x[n-3]) mod m   becomes   c[n] = p c[n-i] + q c[n-3] + K (mod m)
+// on c = x - h with K = (p + q - 1) h mod m, the representative nearest zero.
+template <int G>
+struct F64Consts {
+    static constexpr bool k32 = G == kGen32k3a;
+    static constexpr uint32_t m1w = k32 ? kM1 : kP1, m2w = k32 ? kM2 : kP2;
+    static constexpr int64_t p1w = k32 ? kA12 : kB12, q1w = k32 ? -static_cast<int64_t>(kA13N) : kB13;
+    static constexpr int64_t p2w = k32 ? kA21 : kB21, q2w = k32 ? -static_cast<int64_t>(kA23N) : kB23;
+    static constexpr uint32_t hw = (m2w - 1) / 2;
+    static constexpr double m1 = m1w, h = hw;
+    static constexpr double centred(int64_t x, int64_t m) {
+        x %= m;
+        if (2 * x > m) x -= m;
+        if (2 * x < -m) x += m;
+        return static_cast<double>(x);
+    }
+};
 
-// p an integer with |p| < 2^53 -> an integer r = p (mod m) with
-// |r| <= m/2 + 4, exactly: q is the nearest quotient (off by at most one),
-// and p - q*m is exact in one FMA.
-__device__ __forceinline__ double f64_rem(double p, double m, double inv_m) {
-    double q = __builtin_rint(p * inv_m);
+// The constants of a step, held in registers.  The empty asm hides their
+// values: with literals the compiler turns the multiply-adds into the
+// accumulating form, which overwrites its addend, and copies every addend
+// first (115 VALU instructions per six fp64 uniforms instead of 84).  Made
+// once, before the loops.
+template <int G>
+struct F64Regs {
+    using C = F64Consts<G>;
+    double p1, q1, K1, p2, q2, K2, m1, m2, inv1, inv2;
+    double shift;   // 1.5 2^52: adding it rounds to an integer
+    double shift_v; // the same in vector registers (an instruction reads one scalar pair)
+    __device__ __forceinline__ F64Regs()
+        : p1(C::p1w), q1(C::q1w), K1(C::centred((C::p1w + C::q1w - 1) * C::hw, C::m1w)), p2(C::p2w), q2(C::q2w),
+          K2(C::centred((C::p2w + C::q2w - 1) * C::hw, C::m2w)), m1(C::m1w), m2(C::m2w), inv1(1.0 / C::m1w),
+          inv2(1.0 / C::m2w), shift(0x1.8p52), shift_v(0x1.8p52) {
+        asm("" : "+s"(p1), "+s"(q1), "+s"(p2), "+s"(q2), "+s"(m1), "+s"(m2), "+s"(inv1), "+s"(inv2), "+s"(shift));
+        asm("" : "+v"(K1), "+v"(K2), "+v"(shift_v));
+    }
+};
+
+// p an integer, |p| <= (p1 + |q1|) (m/2 + 2^14) + m/2 < 2^53 -> an integer
+// r = p (mod m) with |r| <= m/2 + 1, exactly.  The quotient is one FMA onto
+// 1.5 2^52, whose last place is 1, so it is p/m rounded once, with the
+// error of the constant 1/m alone before the rounding; p - q*m is exact.
+//
+// Where |p| < 0.906 2^20 m the result is the residue in [-(m-1)/2, (m-1)/2]:
+// p/m is at least 1/(2m) > 2^-33 away from any half integer (m is odd) and
+// the constant's error moves it by at most 2^-53 |p/m| < 2^-33.14.
+template <int G>
+__device__ __forceinline__ double f64_centred(double p, double m, double inv_m, const F64Regs<G>& k) {
+    const double q = __builtin_fma(p, inv_m, k.shift_v) - k.shift;
     return __builtin_fma(-q, m, p);
 }
 
-// |r| <= m/2 + 4 -> r mod m in [0, m): floor(r/m) is -1 or 0.
-__device__ __forceinline__ double f64_canon(double r, double m, double inv_m) {
-    double t = __builtin_floor(r * inv_m);
-    return __builtin_fma(-t, m, r);
+// 1 where the integer d is 0 or less, 0 where it is 1 or more: 1 - d clamped
+// to [0, 1], one instruction.
+__device__ __forceinline__ double f64_wraps(double d) {
+    return __builtin_fmin(__builtin_fmax(1.0 - d, 0.0), 1.0);
 }
 
-// Component 1 is carried as any residue with |x| <= m1/2 + 4 (its value only
-// matters mod m1); component 2 is kept in [0, m2) because z uses its value.
-// Products stay below 2^53 in magnitude either way, so every FMA is exact.
-struct F64Engine {
-    double a0, a1, a2, b0, b1, b2;
+// One step of a component costs two multiply-adds, the quotient's two
+// instructions and the remainder's one; z costs three more: 13 per integer,
+// 14 per fp64 uniform (17 and 18 with component 2 kept in [0, m2) by a floor
+// step and z found by another: 2^28 f32 uniforms of 65,536 streams 203 -> 179
+// us, 2^30 fp64 normals 1844 -> 1771 us; MRG31k3p took about 30 as 32-bit
+// rotations and folds, and its 10^8 normals of the paper's example 225 -> 205
+// us).  Issue-bound: every instruction here takes one slot.
+//
+// Component 1 may be any residue with |a| <= m1/2 + 1 (its class mod m1 is
+// what matters).  Component 2 must be one value per class, because z uses it:
+// its |p| is at most (p2 + |q2| + 1) m2/2 < 0.906 2^20 m2, so f64_centred
+// gives the residue in [-h, h], and x2 = b + h lies in [0, m2).  A state just
+// loaded has a in [-h, m1 - h), a few thousand past m1/2, which the bound on p
+// allows for.
+template <int G>
+struct F64EngineOf {
+    using C = F64Consts<G>;
+    using Regs = F64Regs<G>;
+    double a0, a1, a2, b0, b1, b2;  // (x1[n-3], x1[n-2], x1[n-1]) - h, (x2[...]) - h
 
     __device__ __forceinline__ void load(const uint32_t x[6]) {
-        a0 = x[0]; a1 = x[1]; a2 = x[2]; b0 = x[3]; b1 = x[4]; b2 = x[5];
+        // MRG31k3p's stored state is newest first
+        a0 = x[C::k32 ? 0 : 2] - C::h; a1 = x[1] - C::h; a2 = x[C::k32 ? 2 : 0] - C::h;
+        b0 = x[C::k32 ? 3 : 5] - C::h; b1 = x[4] - C::h; b2 = x[C::k32 ? 5 : 3] - C::h;
+    }
+    static __device__ __forceinline__ uint32_t word1(double a) {  // a + h is below m1: add m1 where negative
+        const double v = a + C::h;
+        return static_cast<uint32_t>(__builtin_fma(f64_wraps(v + 1.0), C::m1, v));
     }
     __device__ __forceinline__ void save(uint32_t x[6]) const {
-        x[0] = static_cast<uint32_t>(f64_canon(a0, kM1d, kInvM1));
-        x[1] = static_cast<uint32_t>(f64_canon(a1, kM1d, kInvM1));
-        x[2] = static_cast<uint32_t>(f64_canon(a2, kM1d, kInvM1));
-        x[3] = static_cast<uint32_t>(b0); x[4] = static_cast<uint32_t>(b1);
-        x[5] = static_cast<uint32_t>(b2);
+        x[C::k32 ? 0 : 2] = word1(a0);
+        x[1] = word1(a1);
+        x[C::k32 ? 2 : 0] = word1(a2);
+        x[C::k32 ? 3 : 5] = static_cast<uint32_t>(b0 + C::h);
+        x[4] = static_cast<uint32_t>(b1 + C::h);
+        x[C::k32 ? 5 : 3] = static_cast<uint32_t>(b2 + C::h);
     }
-    static __device__ __forceinline__ double kernel(double& o1, double m2_1, double& o2, double n1_2) {
-        double p1 = __builtin_fma(static_cast<double>(kA12), m2_1, -(static_cast<double>(kA13N) * o1));
-        double p2 = __builtin_fma(static_cast<double>(kA21), n1_2, -(static_cast<double>(kA23N) * o2));
-        double x1 = f64_rem(p1, kM1d, kInvM1);
-        double x2 = f64_canon(f64_rem(p2, kM2d, kInvM2), kM2d, kInvM2);
-        o1 = x1;
-        o2 = x2;
-        // z = d mod m1 in [1, m1], d = x1 - x2 in [-(1.5 m1 + 4), m1/2 + 4]:
-        // t = floor((d-1)/m1) in {-2, -1, 0}.  Near a multiple of m1 the
-        // quotient differs from it by at least 1/m1, far above the rounding
-        // of the FMA, so t is exact.
-        double d = x1 - x2;
-        double t = __builtin_floor(__builtin_fma(d, kInvM1, -kInvM1));
-        return __builtin_fma(-t, kM1d, d);
+    // o1 = c1[n-3] (becomes c1[n]), m2_1 = c1[n-2], o2 = c2[n-3] (becomes
+    // c2[n]), n1_2 = c2[n-1]; returns z in [1, m1].
+    static __device__ __forceinline__ double kernel(const Regs& k, double& o1, double m2_1, double& o2, double n1_2) {
+        const double t1 = __builtin_fma(k.q1, o1, k.K1);
+        const double t2 = __builtin_fma(k.q2, o2, k.K2);
+        o1 = f64_centred<G>(__builtin_fma(k.p1, m2_1, t1), k.m1, k.inv1, k);
+        o2 = f64_centred<G>(__builtin_fma(k.p2, n1_2, t2), k.m2, k.inv2, k);
+        // h cancels: d = x1 - x2 (mod m1) with |d| <= (m1 + m2)/2 + 1 < m1
+        const double d = o1 - o2;
+        return __builtin_fma(f64_wraps(d), k.m1, d);
     }
     template <int P>
-    __device__ __forceinline__ double step() {
-        if (P == 0) return kernel(a0, a1, b0, b2);
-        if (P == 1) return kernel(a1, a2, b1, b0);
-        return kernel(a2, a0, b2, b1);
+    __device__ __forceinline__ double step(const Regs& k) {
+        if (P == 0) return kernel(k, a0, a1, b0, b2);
+        if (P == 1) return kernel(k, a1, a2, b1, b0);
+        return kernel(k, a2, a0, b2, b1);
     }
-    __device__ __forceinline__ double step_rot() {
-        double z = kernel(a0, a1, b0, b2);
+    __device__ __forceinline__ double step_rot(const Regs& k) {
+        double z = kernel(k, a0, a1, b0, b2);
         double t = a0; a0 = a1; a1 = a2; a2 = t;
         t = b0; b0 = b1; b1 = b2; b2 = t;
         return z;

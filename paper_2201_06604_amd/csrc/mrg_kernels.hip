@@ -81,8 +81,8 @@ __device__ __forceinline__ void dev_jump(uint32_t x[6], uint64_t e) {
 template <int G = kGen32k3a>
 __device__ __forceinline__ void dev_jump_digits(uint32_t x[6], uint64_t e) {
     const StepDigitsF64& T = G == kGen32k3a ? g_stepdig : g_stepdig31;
-    constexpr double m1 = G == kGen32k3a ? kM1d : static_cast<double>(kP1);
-    constexpr double m2 = G == kGen32k3a ? kM2d : static_cast<double>(kP2);
+    constexpr double m1 = G == kGen32k3a ? static_cast<double>(kM1) : static_cast<double>(kP1);
+    constexpr double m2 = G == kGen32k3a ? static_cast<double>(kM2) : static_cast<double>(kP2);
     double v1[3] = {static_cast<double>(x[0]), static_cast<double>(x[1]), static_cast<double>(x[2])};
     double v2[3] = {static_cast<double>(x[3]), static_cast<double>(x[4]), static_cast<double>(x[5])};
     for (int d = 0; e; ++d, e >>= 6) {
@@ -230,10 +230,8 @@ __device__ __forceinline__ void main_rows(const GenLaunch& L, uint32_t by, uint6
 template <int DIST, int DTYPE, int ARITH, int SPL, bool NT, int LOCK = 0>
 __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uint32_t by) {
     static_assert(LOCK == 0 || LOCK == 1 || LOCK == 3, "barriers per iteration");
-    using Engine = typename std::conditional<
-        ARITH == kArith31, Engine31,
-        typename std::conditional<ARITH == kArithF64, F64Engine, IntEngine>::type>::type;
     constexpr int G = ARITH == kArith31 ? kGen31k3p : kGen32k3a;
+    using Engine = typename std::conditional<ARITH == kArithInt, IntEngine, F64EngineOf<G>>::type;
     using T = typename ElemOf<DTYPE>::T;
     constexpr uint32_t ESZ = sizeof(T);
     constexpr uint32_t WS = 64 * SPL;                   // streams per wave
@@ -257,6 +255,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
     // here has u0 >= q (>= q/2 for pairs), so kend == u0: no main-loop rows.
     if (u0 >= units[0]) return;
 
+    const typename Engine::Regs kr;
     Engine e[SPL];
 #pragma unroll
     for (int i = 0; i < SPL; ++i) {
@@ -266,11 +265,8 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
         for (int w = 0; w < 6; ++w) x[w] = rec[w];
         const uint64_t jump = L.offset + u0 * kSpu;
         if (jump) {
-            // MRG31k3p keeps its per-bit jump here: with the digit tables
-            // its main loop compiled about 5% slower at 262,144 x 4,096
-            // (770 against 810 G uniforms/s), where no jump even runs
-            if constexpr (ARITH == kArithF64) dev_jump_digits<G>(x, jump);
-            else dev_jump<G>(x, jump);
+            if constexpr (ARITH == kArithInt) dev_jump<G>(x, jump);
+            else dev_jump_digits<G>(x, jump);
         }
         e[i].load(x);
     }
@@ -303,19 +299,19 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
             if constexpr (LOCK == 3) __builtin_amdgcn_s_barrier();
         };
         for (; k + 3 <= kend; k += 3) {
-            pair([](Engine& g, double& x, double& y) {
-                auto z0 = g.template step<0>();
-                auto z1 = g.template step<1>();
+            pair([&kr](Engine& g, double& x, double& y) {
+                auto z0 = g.template step<0>(kr);
+                auto z1 = g.template step<1>(kr);
                 box_muller<G, DTYPE>(z0, z1, x, y);
             });
-            pair([](Engine& g, double& x, double& y) {
-                auto z2 = g.template step<2>();
-                auto z3 = g.template step<0>();
+            pair([&kr](Engine& g, double& x, double& y) {
+                auto z2 = g.template step<2>(kr);
+                auto z3 = g.template step<0>(kr);
                 box_muller<G, DTYPE>(z2, z3, x, y);
             });
-            pair([](Engine& g, double& x, double& y) {
-                auto z4 = g.template step<1>();
-                auto z5 = g.template step<2>();
+            pair([&kr](Engine& g, double& x, double& y) {
+                auto z4 = g.template step<1>(kr);
+                auto z5 = g.template step<2>(kr);
                 box_muller<G, DTYPE>(z4, z5, x, y);
             });
             if constexpr (LOCK == 1) __builtin_amdgcn_s_barrier();
@@ -324,8 +320,8 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
             Pack<T, SPL> px, py;
 #pragma unroll
             for (int i = 0; i < SPL; ++i) {
-                auto z0 = e[i].step_rot();
-                auto z1 = e[i].step_rot();
+                auto z0 = e[i].step_rot(kr);
+                auto z1 = e[i].step_rot(kr);
                 double x, y;
                 box_muller<G, DTYPE>(z0, z1, x, y);
                 px.v[i] = narrow<DTYPE>(x);
@@ -342,8 +338,8 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
 #pragma unroll
             for (int i = 0; i < SPL; ++i) {
                 if (k < units[i]) {
-                    auto z0 = e[i].step_rot();
-                    auto z1 = e[i].step_rot();
+                    auto z0 = e[i].step_rot(kr);
+                    auto z1 = e[i].step_rot(kr);
                     double x, y;
                     box_muller<G, DTYPE>(z0, z1, x, y);
                     if (2 * k < cnt[i]) store_1<T, NT>(row_rsrc(row, nrec), voff + i * ESZ, narrow<DTYPE>(x));
@@ -358,9 +354,9 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
             Pack<T, SPL> p0, p1, p2;
 #pragma unroll
             for (int i = 0; i < SPL; ++i) {
-                p0.v[i] = value1<DIST, DTYPE, G>(e[i].template step<0>(), inv_rate);
-                p1.v[i] = value1<DIST, DTYPE, G>(e[i].template step<1>(), inv_rate);
-                p2.v[i] = value1<DIST, DTYPE, G>(e[i].template step<2>(), inv_rate);
+                p0.v[i] = value1<DIST, DTYPE, G>(e[i].template step<0>(kr), inv_rate);
+                p1.v[i] = value1<DIST, DTYPE, G>(e[i].template step<1>(kr), inv_rate);
+                p2.v[i] = value1<DIST, DTYPE, G>(e[i].template step<2>(kr), inv_rate);
             }
             store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, p0);
             row += rowstep;
@@ -375,7 +371,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
         for (; k < kend; ++k) {
             Pack<T, SPL> p;
 #pragma unroll
-            for (int i = 0; i < SPL; ++i) p.v[i] = value1<DIST, DTYPE, G>(e[i].step_rot(), inv_rate);
+            for (int i = 0; i < SPL; ++i) p.v[i] = value1<DIST, DTYPE, G>(e[i].step_rot(kr), inv_rate);
             store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, p);
             row += rowstep;
         }
@@ -385,7 +381,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
             for (int i = 0; i < SPL; ++i)
                 if (k < units[i])
                     store_1<T, NT>(row_rsrc(row, nrec), voff + i * ESZ,
-                                   value1<DIST, DTYPE, G>(e[i].step_rot(), inv_rate));
+                                   value1<DIST, DTYPE, G>(e[i].step_rot(kr), inv_rate));
             row += rowstep;
         }
     }
@@ -1296,15 +1292,6 @@ hipError_t launch_generate(const GenLaunch& L, hipStream_t s) {
 // columns of the same rows in step.  The lane jumps its stream(s) to the
 // chunk's first visit; with one chunk per work-item it writes the state back,
 // otherwise paper_finalize_kernel does, after the launch.
-template <int G>
-struct EngineOf {
-    using T = F64Engine;
-};
-template <>
-struct EngineOf<kGen31k3p> {
-    using T = Engine31;
-};
-
 __device__ __forceinline__ uint64_t paper_stream_of(int dist, uint32_t g0, uint32_t g1, uint32_t G0, uint32_t G1) {
     return (dist == kUniform || dist == kRaw) ? g0 + static_cast<uint64_t>(G0) * g1
                                               : static_cast<uint64_t>(g0) * G1 + g1;
@@ -1323,7 +1310,7 @@ __host__ __device__ inline uint64_t paper_lanes_per_chunk(const PaperLaunch& L) 
 template <int DIST, int DTYPE, int G>
 __global__ void __launch_bounds__(256) paper_kernel(PaperLaunch L) {
     if constexpr (DIST == kNormal || DIST == kExponential) stage_tables();
-    using Engine = typename EngineOf<G>::T;
+    using Engine = F64EngineOf<G>;
     using T = typename ElemOf<DTYPE>::T;
     const uint64_t id = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     // lanes per chunk, a whole number of waves: every wave lies in one chunk,
@@ -1352,6 +1339,7 @@ __global__ void __launch_bounds__(256) paper_kernel(PaperLaunch L) {
     uint32_t* ra = L.streams + paper_stream_of(DIST, g0, g1, L.G0, L.G1) * 18;
     uint32_t* rb_rec = DIST == kNormal ? L.streams + paper_stream_of(DIST, g0, g1 + 1, L.G0, L.G1) * 18 : ra;
     uint32_t x[6];
+    const typename Engine::Regs kr;
     Engine ea, eb;
 #pragma unroll
     for (int w = 0; w < 6; ++w) x[w] = ra[w];
@@ -1371,14 +1359,14 @@ __global__ void __launch_bounds__(256) paper_kernel(PaperLaunch L) {
         T* row = out + (g0 + static_cast<uint64_t>(i) * L.G0) * L.npad;
         for (uint32_t j = j0, c = g1 + j0 * L.G1; j < j1; ++j, c += L.G1) {
             if constexpr (DIST == kNormal) {
-                auto z1 = ea.step_rot();
-                auto z2 = eb.step_rot();
+                auto z1 = ea.step_rot(kr);
+                auto z2 = eb.step_rot(kr);
                 double xv, yv;
                 box_muller<G, DTYPE>(z1, z2, xv, yv);
                 __builtin_nontemporal_store(narrow<DTYPE>(xv), row + c);
                 __builtin_nontemporal_store(narrow<DTYPE>(yv), row + c + 1);
             } else {
-                __builtin_nontemporal_store(value1<DIST, DTYPE, G>(ea.step_rot(), inv_rate), row + c);
+                __builtin_nontemporal_store(value1<DIST, DTYPE, G>(ea.step_rot(kr), inv_rate), row + c);
             }
         }
         if (L.n_cb > 1) break;  // a column block covers one row

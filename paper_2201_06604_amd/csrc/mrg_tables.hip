@@ -51,6 +51,7 @@ __device__ __forceinline__ double log_factorial(int n) { return g_logfact[n]; }
 template <int MAXD, int NCK, typename Engine>
 __device__ double sample_table(Engine& e, double norm, int I, int J, const int32_t* r, const int32_t* c, int32_t* tab,
                                int ld, HyperCk ck) {
+    const typename Engine::Regs kr;
     int32_t crem[MAXD];
     for (int j = 0; j < J; ++j) crem[j] = c[j];
     double stat = 0.0;
@@ -59,7 +60,7 @@ __device__ double sample_table(Engine& e, double norm, int I, int J, const int32
         int64_t Np = 0;  // units left in columns j..J-1 over rows i..I-1
         for (int j = 0; j < J; ++j) Np += crem[j];
         for (int j = 0; j < J - 1; ++j) {
-            const double u = to_f64(e.step_rot()) * norm;
+            const double u = to_f64(e.step_rot(kr)) * norm;
             const int x = hyper_invert_ck<NCK>(u, Np, crem[j], rrem, ck);
             if (tab) tab[i * ld + j] = x;
             stat -= log_factorial(x);
@@ -81,13 +82,8 @@ __device__ double sample_table(Engine& e, double norm, int I, int J, const int32
 // The engine and the scale 1/(m1+1) of generator G.
 template <int G>
 struct GenOf {
-    using Engine = F64Engine;
-    static constexpr double norm = kNorm;
-};
-template <>
-struct GenOf<kGen31k3p> {
-    using Engine = Engine31;
-    static constexpr double norm = kNorm31;
+    using Engine = F64EngineOf<G>;
+    static constexpr double norm = G == kGen32k3a ? kNorm : kNorm31;
 };
 
 // Table t: shape I[t] x J[t] (<= 5 x 5), margins rows[t][5], cols[t][5],
