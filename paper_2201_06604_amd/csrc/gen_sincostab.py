@@ -1,12 +1,12 @@
-"""Write mrg_sincostab.h: the 129-entry table of sincospi_unit (mrg_engine.h).
+"""Write mrg_sincostab.h: the 257-entry table of sincospi_unit (mrg_engine.h).
 
     python paper_2201_06604_amd/csrc/gen_sincostab.py
 
-The Box-Muller angle argument t = 2 u2 lies in (0, 2).  Entry j (0 <= j <= 128)
-holds sin(pi j/64) and cos(pi j/64), each as hi + lo (hi the double nearest
-the value, lo the double nearest the remainder); at j = 0, 32, 64, 96, 128 the
-values are exactly 0 or +-1 and lo is 0.  sincospi_unit takes j = rint(64 t)
-and d = t - j/64 (exact, |d| <= 1/128) and combines the entry with sin(pi d)
+The Box-Muller angle argument t = 2 u2 lies in (0, 2).  Entry j (0 <= j <= 256)
+holds sin(pi j/128) and cos(pi j/128), each as hi + lo (hi the double nearest
+the value, lo the double nearest the remainder); at j = 0, 64, 128, 192, 256 the
+values are exactly 0 or +-1 and lo is 0.  sincospi_unit takes j = rint(128 t)
+and d = t - j/128 (exact, |d| <= 1/256) and combines the entry with sin(pi d)
 and cos(pi d) - 1 by the angle-sum formulas.  pi comes from Machin's formula
 and sin/cos from their Taylor series, all in Python's decimal arithmetic at 60
 significant digits; each stored value is rounded once.
@@ -16,7 +16,7 @@ from decimal import Decimal, getcontext
 
 getcontext().prec = 60
 HERE = os.path.dirname(os.path.abspath(__file__))
-N = 128  # entries j = 0 .. N
+N = 256  # entries j = 0 .. N
 
 
 def atan_inv(x: int) -> Decimal:
@@ -62,22 +62,24 @@ def split(v: Decimal):
 def entries():
     out = []
     for j in range(N + 1):
-        if j % 32 == 0:  # the axes: exact values
-            q = j // 32
+        if j % 64 == 0:  # the axes: exact values
+            q = j // 64
             s = [0.0, 1.0, 0.0, -1.0, 0.0][q]
             c = [1.0, 0.0, -1.0, 0.0, 1.0][q]
-            out.append((s, 0.0, c, 0.0))
+            out.append((s, c, 0.0, 0.0))
             continue
-        sv, cv = sin_cos(PI * j / 64)
-        out.append(split(sv) + split(cv))
+        sv, cv = sin_cos(PI * j / 128)
+        (sh, sl), (ch, cl) = split(sv), split(cv)
+        out.append((sh, ch, sl, cl))
     return out
 
 
 def main():
-    rows = [f"    {{{a.hex()}, {b.hex()}, {c.hex()}, {d.hex()}}},  // j = {j}"
-            for j, (a, b, c, d) in enumerate(entries())]
-    text = """// mrg_sincostab.h -- table of sincospi_unit (mrg_engine.h): for j = 0..128,
-// sin(pi j/64) and cos(pi j/64), each as hi + lo (exact 0 or +-1 on the axes).
+    table = list(enumerate(entries()))
+    hi = [f"    {{{a.hex()}, {b.hex()}}},  // j = {j}" for j, (a, b, _, _) in table]
+    lo = [f"    {{{a.hex()}, {b.hex()}}},  // j = {j}" for j, (_, _, a, b) in table]
+    text = """// mrg_sincostab.h -- table of sincospi_unit (mrg_engine.h): for j = 0..256,
+// sin(pi j/128) and cos(pi j/128), each as hi + lo (exact 0 or +-1 on the axes).
 // Written by gen_sincostab.py (Python decimal arithmetic at 60 digits, each
 // value rounded once); do not edit.
 #pragma once
@@ -86,14 +88,17 @@ namespace mrg355 {
 
 constexpr int kSinCosTabN = %d;
 struct SinCosTable {
-    double e[kSinCosTabN][4];  // (sin hi, sin lo, cos hi, cos lo) of each entry
+    double hi[kSinCosTabN][2];  // (sin, cos) of each entry
+    double lo[kSinCosTabN][2];
 };
 constexpr SinCosTable kSinCosTable = {{
+%s
+}, {
 %s
 }};
 
 }  // namespace mrg355
-""" % (N + 1, "\n".join(rows))
+""" % (N + 1, "\n".join(hi), "\n".join(lo))
     with open(os.path.join(HERE, "mrg_sincostab.h"), "w") as f:
         f.write(text)
 

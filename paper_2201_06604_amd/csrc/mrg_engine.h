@@ -202,49 +202,6 @@ struct F64EngineOf {
 };
 
 // ------------------------------------------------------------- transforms
-// sin(pi t) and cos(pi t) for t = 2u in (0, 2) (the Box-Muller angle).
-// n = rint(2t), r = t - n/2 in [-1/4, 1/4] (exact: t and n/2 are within a
-// factor of two, or n = 0); sin(pi r) and cos(pi r) by their Taylor series in
-// r^2 with pi folded into the coefficients (sine through r^17, cosine through
-// r^16: the next terms are below 2^-58 at |r| = 1/4); the quadrant n mod 4
-// swaps and negates.  mrg_transform_accuracy compares both results with the
-// HIP library's sincospi over any range of generator outputs.
-__device__ __forceinline__ void sincospi_unit_series(double t, double* sp, double* cp) {
-    const double n = __builtin_rint(t + t);
-    const double r = __builtin_fma(n, -0.5, t);
-    const double z = r * r;
-    double ps = 7.952054001475513e-07;
-    ps = __builtin_fma(ps, z, -2.1915353447830217e-05);
-    ps = __builtin_fma(ps, z, 0.00046630280576761255);
-    ps = __builtin_fma(ps, z, -0.0073704309457143504);
-    ps = __builtin_fma(ps, z, 0.08214588661112823);
-    ps = __builtin_fma(ps, z, -0.5992645293207921);
-    ps = __builtin_fma(ps, z, 2.5501640398773455);
-    ps = __builtin_fma(ps, z, -5.16771278004997);
-    ps = __builtin_fma(ps, z, 3.141592653589793);
-    const double sn = r * ps;
-    double pc = 4.303069587032947e-06;
-    pc = __builtin_fma(pc, z, -0.0001046381049248457);
-    pc = __builtin_fma(pc, z, 0.0019295743094039231);
-    pc = __builtin_fma(pc, z, -0.02580689139001406);
-    pc = __builtin_fma(pc, z, 0.2353306303588932);
-    pc = __builtin_fma(pc, z, -1.3352627688545895);
-    pc = __builtin_fma(pc, z, 4.0587121264167685);
-    pc = __builtin_fma(pc, z, -4.934802200544679);
-    const double cs = __builtin_fma(pc, z, 1.0);
-    // quadrant q = n mod 4 (n in 0..4): odd q swaps sine and cosine; the sine
-    // is negative for q = 2, 3 (bit 1 of n) and the cosine for q = 1, 2 (bit 1
-    // of n + 1), applied as a flip of the sign bit in the high word
-    const uint32_t ni = static_cast<uint32_t>(static_cast<int>(n));
-    const double s1 = (ni & 1u) ? cs : sn;
-    const double c1 = (ni & 1u) ? sn : cs;
-    const uint32_t sgn_s = (ni << 30) & 0x80000000u;
-    const uint32_t sgn_c = ((ni + 1u) << 30) & 0x80000000u;
-    *sp = __hiloint2double(__double2hiint(s1) ^ static_cast<int>(sgn_s), __double2loint(s1));
-    *cp = __hiloint2double(__double2hiint(c1) ^ static_cast<int>(sgn_c), __double2loint(c1));
-}
-
-
 // sqrt(x) for the Box-Muller radius argument x = -2 log(u1) in [2^-32, 47]:
 // never zero, subnormal or non-finite, so the range scaling and special
 // cases of a general square root are left out.  Goldschmidt's iteration from
@@ -265,162 +222,127 @@ __device__ __forceinline__ double sqrt_radius(double x) {
     return __builtin_fma(d, h, g);
 }
 
-// log(u) for the generators' uniforms, u in [2^-33, 1): never zero,
-// subnormal, negative or non-finite, so no special cases.  u = m 2^k with m
-// in [sqrt(1/2), sqrt(2)); f = m - 1 (exact); s = f / d with d = 2 + f;
-// log(m) = 2 atanh(s) = 2s + 2s (s^2/3 + s^4/5 + ... + s^18/19) (|s| <=
-// 0.1716, so the next term is below 2^-55 relative); log(u) = k ln2 + log(m)
-// with ln2 split so that k * ln2_hi is exact.  d = 2 + f is rounded (f can
-// carry a bit below d's last place), so s has up to about one ulp of relative
-// error whatever the division does; the quotient itself uses the hardware
-// reciprocal (relative error below 5e-8 on these divisors), one Newton step
-// and one residual correction q += (f - q d) y, which leave a quotient of the
-// rounded d accurate far below an ulp.  mrg_transform_accuracy compares the
-// result with the HIP library's log over any range of generator outputs.
-// SCALE (1, -1, 2 or -2) multiplies the result: it is folded into the last
-// three steps' constants, and scaling by a power of two commutes with
-// rounding, so log_unit<SCALE>(u) is bit for bit SCALE * log_unit(u).
-template <int SCALE = 1>
-__device__ __forceinline__ double log_unit_series(double u) {
-    static_assert(SCALE == 1 || SCALE == -1 || SCALE == 2 || SCALE == -2, "power-of-two scale");
-    int k = __builtin_amdgcn_frexp_exp(u);          // u = mant * 2^k, mant in [1/2, 1)
-    double m = __builtin_amdgcn_frexp_mant(u);
-    // below sqrt(1/2) the mantissa is doubled (an exponent step, exact) and k
-    // lowered: one integer select and an ldexp rather than a 64-bit select
-    const int lo = m < 0.70710678118654752440 ? 1 : 0;
-    m = __builtin_amdgcn_ldexp(m, lo);
-    k -= lo;
-    const double f = m - 1.0;
-    const double d = 2.0 + f;
-    double y = __builtin_amdgcn_rcp(d);
-    const double e = __builtin_fma(-d, y, 1.0);
-    y = __builtin_fma(e, y, y);
-    double q = f * y;
-    q = __builtin_fma(__builtin_fma(-q, d, f), y, q);  // s = f / d
-    const double z = q * q;
-    double r = 1.0 / 19.0;
-    r = __builtin_fma(r, z, 1.0 / 17.0);
-    r = __builtin_fma(r, z, 1.0 / 15.0);
-    r = __builtin_fma(r, z, 1.0 / 13.0);
-    r = __builtin_fma(r, z, 1.0 / 11.0);
-    r = __builtin_fma(r, z, 1.0 / 9.0);
-    r = __builtin_fma(r, z, 1.0 / 7.0);
-    r = __builtin_fma(r, z, 1.0 / 5.0);
-    r = __builtin_fma(r, z, 1.0 / 3.0);
-    r = r * z;
-    const double s2 = q * (2.0 * SCALE);
-    const double log_m = __builtin_fma(s2, r, s2);
-    const double kd = static_cast<double>(k);
-    constexpr double kLn2Hi = 6.93147180369123816490e-01;  // ln 2 to 32 bits: k * hi exact for |k| < 2^20
-    constexpr double kLn2Lo = 1.90821492927058770002e-10;  // ln 2 - hi
-    return __builtin_fma(kd, kLn2Hi * SCALE, __builtin_fma(kd, kLn2Lo * SCALE, log_m));
-}
-
-// The tables of log_unit (mrg_logtab.h) and sincospi_unit (mrg_sincostab.h)
-// in LDS: every kernel whose code evaluates the fp64 transforms stages them
-// once per block with stage_tables() (all threads, then a barrier) before any
-// call.
+// The tables of neg2log_unit (mrg_logtab.h) and sincospi_unit
+// (mrg_sincostab.h) in LDS: every kernel whose code evaluates a transform
+// stages what it reads once per block with stage_tables() (all threads, then
+// a barrier) before any call.
+//
+// Entries are pairs of doubles, 16 bytes apart, read with one 16-byte load.
+// Lanes read them at random; with 16 waves on a CU such a load took 6.5
+// cycles a wave, the 24-byte log entries before it (an 8-byte pair load and a
+// single) 13, and two doubles 16 bytes apart in a 32-byte entry (the fp32
+// sine and cosine) 19: LDS was busy for four fifths of an fp32 normal launch.
+// With the shorter functions below (75 -> 72 VALU instructions a pair, 32 -> 30
+// an exponential), 2^30 fp64 normals 1771 -> 1620 us, 2^24 fp32 exponentials
+// and their substream step 28.0 -> 26.5 us, the paper's 10^8 MRG31k3p normals
+// 205 -> 192 us.  Three quarters of an fp64 normal launch is VALU issue.
+typedef double double2v __attribute__((ext_vector_type(2)));
 static __constant__ LogTable g_logtab = kLogTable;
 static __constant__ SinCosTable g_sincostab = kSinCosTable;
 
-__device__ __forceinline__ double* log_table_lds() {
-    __shared__ double tab[kLogTabN * 3];
+__device__ __forceinline__ double2v* log_table_lds() {
+    __shared__ double2v tab[kLogTabN];
     return tab;
 }
 
-__device__ __forceinline__ double* sincos_table_lds() {
-    __shared__ double tab[kSinCosTabN * 4];
+__device__ __forceinline__ double2v* sincos_table_lds() {
+    __shared__ double2v tab[kSinCosTabN * 2];  // (sin, cos) of each entry, then their low parts
     return tab;
 }
 
-// Every wave writes both tables whole (the same values): loops of fixed trip
-// count over the wave's lanes, with no dependence on the block size (a loop
-// bounded by threadIdx and blockDim made the compiler treat later row addresses
-// as divergent).
-__device__ __forceinline__ void stage_tables() {
-    double* t = log_table_lds();
-    double* c = sincos_table_lds();
+// COUNT pairs from constant memory to LDS, one per lane, the block's waves in
+// turn.  The loop counter is wave-uniform (readfirstlane): a loop bounded by
+// threadIdx and blockDim themselves makes the compiler treat later row
+// addresses as divergent.
+template <int COUNT>
+__device__ __forceinline__ void stage_pairs(double2v* dst, const double (*src)[2]) {
     const int lane = static_cast<int>(threadIdx.x & 63);
-#pragma unroll
-    for (int k = 0; k < kLogTabN * 3 / 64; ++k) {
+    const int first = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int waves = static_cast<int>(blockDim.x >> 6);
+    for (int k = first; k < (COUNT + 63) / 64; k += waves) {
         const int i = lane + 64 * k;
-        t[i] = g_logtab.e[i / 3][i % 3];
+        if (i < COUNT) dst[i] = double2v{src[i][0], src[i][1]};
     }
-#pragma unroll
-    for (int k = 0; k < (kSinCosTabN * 4 + 63) / 64; ++k) {
-        const int i = lane + 64 * k;
-        if (i < kSinCosTabN * 4) c[i] = g_sincostab.e[i / 4][i % 4];
-    }
+}
+
+enum { kStageLog = 0, kStageNormalF32 = 1, kStageNormal = 2 };
+template <int WHAT>
+__device__ __forceinline__ void stage_tables() {
+    stage_pairs<kLogTabN>(log_table_lds(), g_logtab.e);
+    if constexpr (WHAT >= kStageNormalF32) stage_pairs<kSinCosTabN>(sincos_table_lds(), g_sincostab.hi);
+    if constexpr (WHAT >= kStageNormal) stage_pairs<kSinCosTabN>(sincos_table_lds() + kSinCosTabN, g_sincostab.lo);
     __syncthreads();
 }
 
+// x rounded to an integer, as a double and as the low word of the sum that
+// rounds it (0 <= x < 2^31): two instructions for both.
+__device__ __forceinline__ double round_index(double x_scaled_by, double x, uint32_t* i) {
+    const double s = __builtin_fma(x, x_scaled_by, 0x1.8p52);
+    *i = static_cast<uint32_t>(__double2loint(s));
+    return s - 0x1.8p52;
+}
+
 // sin(pi t) and cos(pi t) for t = 2u in (0, 2) (the Box-Muller angle), by
-// table: j = rint(64 t) and d = t - j/64 (exact: t and j/64 are within a
-// factor of two, or j = 0; |d| <= 1/128); with s_j = sin(pi j/64) and
-// c_j = cos(pi j/64) from the table as hi + lo,
+// table: j = rint(128 t) and d = t - j/128 (exact: t and j/128 are within a
+// factor of two, or j = 0; |d| <= 1/256); with s_j = sin(pi j/128) and
+// c_j = cos(pi j/128) from the table as hi + lo,
 // sin(pi t) = s_j + (s_j (cos(pi d) - 1) + c_j sin(pi d))
 // and cos(pi t) = c_j + (c_j (cos(pi d) - 1) - s_j sin(pi d)), where
-// sin(pi d) runs through d^7 and cos(pi d) - 1 through d^6 (the next terms
-// are below 2^-60 of sin(pi d) and 3.3e-18 in absolute value at |d| = 1/128:
-// even where cos(pi t) is smallest beside a nonzero c_j, j = 31 or 33, that is
-// under 2^-57 of the result).  On the axes (j a multiple
-// of 32) the table holds exact zeros and ones, so results near the zeros of
-// sin and cos keep their relative accuracy.  mrg_transform_accuracy compares
-// both results with the HIP library's sincospi over any range of generator
+// sin(pi d) runs through d^5 with the d^7 term folded into the lower ones by
+// Chebyshev's polynomial on d^2 <= 2^-16 (2^-55 of it is left) and cos(pi d) - 1
+// through d^6 (the next term is below 2^-65).  On the axes (j a multiple of
+// 64) the table holds exact zeros and ones, so results near the zeros of sin
+// and cos keep their relative accuracy.  mrg_transform_accuracy compares both
+// results with the HIP library's sincospi over any range of generator
 // outputs.
 __device__ __forceinline__ void sincospi_unit(double t, double* sp, double* cp) {
-    const double jd = __builtin_rint(t * 64.0);
-    const double d = __builtin_fma(jd, -1.0 / 64.0, t);
-    const double* e = sincos_table_lds() + 4 * static_cast<int>(jd);
+    uint32_t j;
+    const double jd = round_index(128.0, t, &j);
+    const double d = __builtin_fma(jd, -1.0 / 128.0, t);
+    const double2v h = sincos_table_lds()[j], l = sincos_table_lds()[kSinCosTabN + j];
     const double z = d * d;
-    double ps = -0.5992645293207921;  // -pi^7/7!
-    ps = __builtin_fma(ps, z, 2.5501640398773455);  // pi^5/5!
-    ps = __builtin_fma(ps, z, -5.16771278004997);   // -pi^3/3!
+    double ps = 2.550150323800777;                  // pi^5/5! - 3/2 2^-16 pi^7/7!
+    ps = __builtin_fma(ps, z, -5.167712779971486);  // -pi^3/3! + 9/16 2^-32 pi^7/7!
     ps = __builtin_fma(ps, z, 3.141592653589793);   // pi
     const double sd = d * ps;
     double pc = -1.3352627688545895;                // -pi^6/6!
     pc = __builtin_fma(pc, z, 4.0587121264167685);  // pi^4/4!
     pc = __builtin_fma(pc, z, -4.934802200544679);  // -pi^2/2!
     const double cm1 = z * pc;
-    const double sh = e[0], sl = e[1], ch = e[2], cl = e[3];
-    *sp = sh + __builtin_fma(sh, cm1, __builtin_fma(ch, sd, sl));
-    *cp = ch + __builtin_fma(ch, cm1, __builtin_fma(-sh, sd, cl));
+    *sp = h.x + __builtin_fma(h.x, cm1, __builtin_fma(h.y, sd, l.x));
+    *cp = h.y + __builtin_fma(h.y, cm1, __builtin_fma(-h.x, sd, l.y));
 }
 
-// log(u) for the generators' uniforms, u in [2^-33, 1), by table: u = m 2^k
-// with m in [1/2, 1); the top 9 fraction bits of m pick an interval of width
-// 1/1024 whose entry holds R, a multiple of 2^-9 near 1/m (R = 1 on the last
-// interval), and -log(R) = hi + lo.  t = m R - 1 is exact (|t| < 2^-9, a
-// multiple of 2^-62), log(m) = -log(R) + log1p(t) with log1p(t) = t + t^2 P(t)
-// through t^6 (the next term, t^7/7, is below 2^-65: under 2^-55 of any
-// result outside the last interval, where |log u| >= 2^-10, and below 2^-54
-// of t on the last one), and k ln2 + hi is exact (hi a multiple of 2^-40,
-// ln2_hi of 2^-32, |k| <= 33).  Near u = 1 (k = 0, R = 1) the result is
-// log1p(t) alone, accurate relative to its own size.
-// SCALE (1, -1, 2 or -2) multiplies the result exactly.
-// mrg_transform_accuracy compares it with the HIP library's log over any
-// range of generator outputs.
-template <int SCALE = 1>
-__device__ __forceinline__ double log_unit(double u) {
-    static_assert(SCALE == 1 || SCALE == -1 || SCALE == 2 || SCALE == -2, "power-of-two scale");
+constexpr double kLn2Hi = 6.93147180369123816490e-01;  // ln 2 to 32 bits: k * hi exact
+constexpr double kLn2Lo = 1.90821492927058770002e-10;  // ln 2 - hi
+
+// -2 log(u) for the generators' uniforms, u in [2^-33, 1) -- never zero,
+// subnormal, negative or non-finite -- by table: u = m 2^k with m in [1/2, 1);
+// the top 9 fraction bits of m pick an interval of width 1/1024 whose entry
+// holds -2 R, R near 1/m (R = 1 on the last interval), and 2 log(R) (within
+// 2^-62, and 2^-54 of the result).  s = 2 - 2 m R = -2 t with |t| <= 2^-10
+// (1 + 2^-4), and -2 log(m) = 2 log(R) - 2 log1p(t), where
+// log1p(t) = t + t^2 P(t) through t^5 with the t^6 term folded into P by
+// Chebyshev's polynomial (2^-55 of t is left at |t| = 2^-10) and
+// -2 log1p(t) = s + s^2 Q(s).  -2 k ln2_hi + 2 log(R) is exact (multiples of
+// 2^-31 and 2^-47 below 2^6).  Near u = 1 (k = 0, R = 1) the result is
+// s + s^2 Q(s) alone, accurate relative to its own size.  The factor -2, the
+// radius's, is in the tables and constants; an exponential takes half of it
+// with its rate.  15 instructions and one LDS load.
+__device__ __forceinline__ double neg2log_unit(double u) {
     const int k = __builtin_amdgcn_frexp_exp(u);
     const double m = __builtin_amdgcn_frexp_mant(u);  // [1/2, 1)
     static_assert(kLogTabN == 512, "the index takes the top 9 fraction bits of m");
     const uint32_t j = (static_cast<uint32_t>(__double2hiint(m)) >> 11) & (kLogTabN - 1);
-    const double* e = log_table_lds() + 3 * j;
-    const double t = __builtin_fma(m, e[0], -1.0);
-    double p = -1.0 / 6.0;
-    p = __builtin_fma(p, t, 1.0 / 5.0);
-    p = __builtin_fma(p, t, -1.0 / 4.0);
-    p = __builtin_fma(p, t, 1.0 / 3.0);
-    p = __builtin_fma(p, t, -1.0 / 2.0);
-    const double q = (t * t) * p;
+    const double2v e = log_table_lds()[j];
+    const double s = __builtin_fma(m, e.x, 2.0);
+    double q = 0x1.999999999999ap-7;                   // 1/80
+    q = __builtin_fma(q, s, 0x1.00000aaaaaaabp-5);     // 1/32 + 2^-20/48
+    q = __builtin_fma(q, s, 0x1.5555555555555p-4);     // 1/12
+    q = __builtin_fma(q, s, 0x1.ffffffffffeabp-3);     // 1/4 - 2^-40/96
     const double kd = static_cast<double>(k);
-    constexpr double kLn2Hi = 6.93147180369123816490e-01;  // ln 2 to 32 bits: k * hi exact
-    constexpr double kLn2Lo = 1.90821492927058770002e-10;  // ln 2 - hi
-    const double a = __builtin_fma(kd, kLn2Hi, e[1]);
-    const double lo = __builtin_fma(kd, kLn2Lo, e[2]);
-    return (a + (t + (q + lo))) * SCALE;
+    const double lo = __builtin_fma(s * s, q, kd * (-2.0 * kLn2Lo));
+    return __builtin_fma(kd, -2.0 * kLn2Hi, e.y) + (s + lo);
 }
 
 // ----------------------------------------------- transforms for fp32 output
@@ -433,24 +355,20 @@ __device__ __forceinline__ double log_unit(double u) {
 // float is then under 4e-7 of max(|value|, 1), against the 1e-6 fp32
 // tolerance.
 
-// log(u) by log_unit's table (staged in LDS by the calling kernel): t = m R - 1
-// exact, |t| < 2^-9, and log1p(t) through t^3 (the next term, t^4/4 < 2^-38,
-// is below 2^-28 of any result outside the last interval, where
-// |log u| >= 2^-10, and below 2^-29 of t on the last one); -log R's low part
-// (below 2^-40) and the low bits of ln 2 are left out (below 2^-30 of the
-// result).  Near u = 1 (k = 0, R = 1) the result is log1p(t) alone, accurate
-// relative to its own size.
-template <int SCALE = 1>
-__device__ __forceinline__ double log_unit_f32out(double u) {
-    static_assert(SCALE == 1 || SCALE == -1 || SCALE == 2 || SCALE == -2, "power-of-two scale");
+// -2 log(u) by neg2log_unit's table: log1p(t) through t^3 (the next term,
+// t^4/4 < 2^-41, is below 2^-31 of any result outside the last interval, where
+// |log u| >= 2^-10, and of t on the last one); the low bits of ln 2 are left
+// out (below 2^-31 of the result).  Near u = 1 (k = 0, R = 1) the result is
+// -2 log1p(t) alone, accurate relative to its own size.
+__device__ __forceinline__ double neg2log_unit_f32out(double u) {
     const int k = __builtin_amdgcn_frexp_exp(u);
     const double m = __builtin_amdgcn_frexp_mant(u);  // [1/2, 1)
     const uint32_t j = (static_cast<uint32_t>(__double2hiint(m)) >> 11) & (kLogTabN - 1);
-    const double* e = log_table_lds() + 3 * j;
-    const double t = __builtin_fma(m, e[0], -1.0);
-    const double q = (t * t) * __builtin_fma(t, 1.0 / 3.0, -0.5);
+    const double2v e = log_table_lds()[j];
+    const double s = __builtin_fma(m, e.x, 2.0);
+    const double q = __builtin_fma(s * s, __builtin_fma(s, 1.0 / 12.0, 0.25), s);
     constexpr double kLn2 = 6.93147180559945286227e-01;
-    return (__builtin_fma(static_cast<double>(k), kLn2, e[1]) + (t + q)) * SCALE;
+    return __builtin_fma(static_cast<double>(k), -2.0 * kLn2, e.y) + q;
 }
 
 // sqrt(x) for the radius argument, x in [2^-32, 47]: the hardware reciprocal
@@ -463,23 +381,22 @@ __device__ __forceinline__ double sqrt_radius_f32out(double x) {
     return __builtin_fma(d, 0.5 * y, g);
 }
 
-// sin(pi t), cos(pi t) by sincospi_unit's table (staged in LDS by the calling
-// kernel, the high parts only): d = t - j/64, |d| <= 1/128, sin(pi d) through
-// d^3 (next term below 3e-9 of it) and cos(pi d) - 1 through d^2 (next term
-// below 1.5e-8 in absolute value; beside the zero of cos(pi t) it is scaled
-// by |c_j| <= 0.05, under 4e-8 of the result there).  On the axes the table
-// holds exact zeros and ones, so results near the zeros of sin and cos keep
-// their relative accuracy.
+// sin(pi t), cos(pi t) by sincospi_unit's table (the high parts only):
+// d = t - j/128, |d| <= 1/256, sin(pi d) through d^3 (next term below 2e-10 of
+// it) and cos(pi d) - 1 through d^2 (next term below 1e-9 in absolute value;
+// beside the zero of cos(pi t) it is scaled by |c_j| <= 0.025, under 4e-9 of
+// the result there).  On the axes the table holds exact zeros and ones, so
+// results near the zeros of sin and cos keep their relative accuracy.
 __device__ __forceinline__ void sincospi_unit_f32out(double t, double* sp, double* cp) {
-    const double jd = __builtin_rint(t * 64.0);
-    const double d = __builtin_fma(jd, -1.0 / 64.0, t);
-    const double* e = sincos_table_lds() + 4 * static_cast<int>(jd);
+    uint32_t j;
+    const double jd = round_index(128.0, t, &j);
+    const double d = __builtin_fma(jd, -1.0 / 128.0, t);
+    const double2v h = sincos_table_lds()[j];
     const double z = d * d;
     const double sd = d * __builtin_fma(z, -5.16771278004997, 3.141592653589793);  // pi d - (pi d)^3/6
     const double cm1 = z * -4.934802200544679;                                     // -(pi d)^2/2
-    const double sh = e[0], ch = e[2];
-    *sp = __builtin_fma(ch, sd, __builtin_fma(sh, cm1, sh));
-    *cp = __builtin_fma(-sh, sd, __builtin_fma(ch, cm1, ch));
+    *sp = __builtin_fma(h.y, sd, __builtin_fma(h.x, cm1, h.x));
+    *cp = __builtin_fma(-h.x, sd, __builtin_fma(h.y, cm1, h.y));
 }
 
 __device__ __forceinline__ double to_f64(uint32_t z) { return static_cast<double>(z); }

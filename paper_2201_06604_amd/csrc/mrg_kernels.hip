@@ -121,7 +121,7 @@ __device__ __forceinline__ constexpr double norm_of() {
 
 // The stored value of one uniform / raw / exponential draw.
 template <int DIST, int DTYPE, int G, typename Z>
-__device__ __forceinline__ typename ElemOf<DTYPE>::T value1(Z z, double inv_rate) {
+__device__ __forceinline__ typename ElemOf<DTYPE>::T value1(Z z, double half_inv_rate) {
     if constexpr (DIST == kRaw) {
         return to_u32(z);
     } else if constexpr (DIST == kUniform && DTYPE == kF32) {
@@ -129,29 +129,35 @@ __device__ __forceinline__ typename ElemOf<DTYPE>::T value1(Z z, double inv_rate
     } else {
         double u = to_f64(z) * norm_of<G>();
         if constexpr (DIST == kExponential) {
-            if constexpr (DTYPE == kF64) return -log_unit(u) * inv_rate;
-            else return static_cast<float>(-log_unit_f32out(u) * inv_rate);
+            if constexpr (DTYPE == kF64) return neg2log_unit(u) * half_inv_rate;
+            else return static_cast<float>(neg2log_unit_f32out(u) * half_inv_rate);
         } else {
             return u;
         }
     }
 }
 
+// What a kernel of one distribution and type stages.
+template <int DIST, int DTYPE>
+__device__ __forceinline__ void stage_for() {
+    if constexpr (DIST == kExponential) stage_tables<kStageLog>();
+    if constexpr (DIST == kNormal) stage_tables<DTYPE == kF64 ? kStageNormal : kStageNormalF32>();
+}
+
 // Box-Muller pair (Algorithm 1) from two consecutive steps of one stream.
-// The factors -2 and 2 are folded into exact power-of-two scalings: -2 log(u1)
-// comes from log_unit<-2>, and 2 u2 = z2 (2 NORM) is the same double as
-// 2 (z2 NORM).  A pair stored as floats (DTYPE kF32) takes the shorter
-// evaluations of the same functions.
+// The factor -2 of the logarithm is in its table and constants, and
+// 2 u2 = z2 (2 NORM) is the same double as 2 (z2 NORM).  A pair stored as
+// floats (DTYPE kF32) takes the shorter evaluations of the same functions.
 template <int G, int DTYPE, typename Z>
 __device__ __forceinline__ void box_muller(Z z1, Z z2, double& x, double& y) {
     const double u1 = to_f64(z1) * norm_of<G>();
     const double t = to_f64(z2) * (2.0 * norm_of<G>());
     double r, s, c;
     if constexpr (DTYPE == kF64) {
-        r = sqrt_radius(log_unit<-2>(u1));
+        r = sqrt_radius(neg2log_unit(u1));
         sincospi_unit(t, &s, &c);
     } else {
-        r = sqrt_radius_f32out(log_unit_f32out<-2>(u1));
+        r = sqrt_radius_f32out(neg2log_unit_f32out(u1));
         sincospi_unit_f32out(t, &s, &c);
     }
     x = r * c;
@@ -271,7 +277,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
         e[i].load(x);
     }
 
-    const double inv_rate = L.param;
+    const double half_inv_rate = L.param;
     const uint64_t rowstep = static_cast<uint64_t>(S) * ESZ;
     const uint64_t rest = static_cast<uint64_t>(S - first) * ESZ;
     const uint32_t nrec = rest > 0xffffffffull ? 0xffffffffu : static_cast<uint32_t>(rest);
@@ -354,9 +360,9 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
             Pack<T, SPL> p0, p1, p2;
 #pragma unroll
             for (int i = 0; i < SPL; ++i) {
-                p0.v[i] = value1<DIST, DTYPE, G>(e[i].template step<0>(kr), inv_rate);
-                p1.v[i] = value1<DIST, DTYPE, G>(e[i].template step<1>(kr), inv_rate);
-                p2.v[i] = value1<DIST, DTYPE, G>(e[i].template step<2>(kr), inv_rate);
+                p0.v[i] = value1<DIST, DTYPE, G>(e[i].template step<0>(kr), half_inv_rate);
+                p1.v[i] = value1<DIST, DTYPE, G>(e[i].template step<1>(kr), half_inv_rate);
+                p2.v[i] = value1<DIST, DTYPE, G>(e[i].template step<2>(kr), half_inv_rate);
             }
             store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, p0);
             row += rowstep;
@@ -371,7 +377,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
         for (; k < kend; ++k) {
             Pack<T, SPL> p;
 #pragma unroll
-            for (int i = 0; i < SPL; ++i) p.v[i] = value1<DIST, DTYPE, G>(e[i].step_rot(kr), inv_rate);
+            for (int i = 0; i < SPL; ++i) p.v[i] = value1<DIST, DTYPE, G>(e[i].step_rot(kr), half_inv_rate);
             store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, p);
             row += rowstep;
         }
@@ -381,7 +387,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
             for (int i = 0; i < SPL; ++i)
                 if (k < units[i])
                     store_1<T, NT>(row_rsrc(row, nrec), voff + i * ESZ,
-                                   value1<DIST, DTYPE, G>(e[i].step_rot(kr), inv_rate));
+                                   value1<DIST, DTYPE, G>(e[i].step_rot(kr), half_inv_rate));
             row += rowstep;
         }
     }
@@ -409,7 +415,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
 // ending their wave (a wave's lane 0 always holds a stream).
 template <int DIST, int DTYPE, int ARITH, int SPL, bool NT, bool LOCK>
 __global__ void __launch_bounds__(1024) gen_kernel(GenLaunch L) {
-    if constexpr (DIST == kNormal || DIST == kExponential) stage_tables();
+    stage_for<DIST, DTYPE>();
     // Block -> (stream block, chunk).  With xcd remapping, consecutive logical
     // blocks (neighbouring row segments) land on one XCD, whose L2 then sees
     // contiguous runs of every row; blocks are dealt to the 8 XCDs in turn.
@@ -613,7 +619,7 @@ __device__ __forceinline__ uint32_t home_rank(const BatchLaunch& B, int cls) {
 // then helps the other classes until every queue is empty.  The three loops
 // run one after another, so their register live ranges never overlap.
 __global__ void __launch_bounds__(256) batch_kernel(BatchLaunch B) {
-    stage_tables();
+    stage_tables<kStageNormal>();
     constexpr uint32_t kNone = 0xffffffffu;
     if (blockIdx.x == 0 && threadIdx.x < 64) B.head->t_start = __builtin_amdgcn_s_memrealtime();
     if (blockIdx.x < B.block_lo[1]) {
@@ -701,7 +707,7 @@ __device__ __forceinline__ uint32_t tile_iters(const BatchLaunch& B, const Batch
 // kind together allows three.
 template <bool NARROW>
 __device__ __forceinline__ void gang_loop(const BatchLaunch& B) {
-    stage_tables();
+    stage_tables<kStageNormal>();
     __shared__ uint32_t next_gang;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t one = lane == 0 ? 1u : 0u;
@@ -1309,7 +1315,7 @@ __host__ __device__ inline uint64_t paper_lanes_per_chunk(const PaperLaunch& L) 
 
 template <int DIST, int DTYPE, int G>
 __global__ void __launch_bounds__(256) paper_kernel(PaperLaunch L) {
-    if constexpr (DIST == kNormal || DIST == kExponential) stage_tables();
+    stage_for<DIST, DTYPE>();
     using Engine = F64EngineOf<G>;
     using T = typename ElemOf<DTYPE>::T;
     const uint64_t id = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -1354,7 +1360,7 @@ __global__ void __launch_bounds__(256) paper_kernel(PaperLaunch L) {
         eb.load(x);
     }
     T* out = static_cast<T*>(L.out);
-    const double inv_rate = L.param;
+    const double half_inv_rate = L.param;
     for (uint32_t i = i0; i < i1; ++i) {
         T* row = out + (g0 + static_cast<uint64_t>(i) * L.G0) * L.npad;
         for (uint32_t j = j0, c = g1 + j0 * L.G1; j < j1; ++j, c += L.G1) {
@@ -1366,7 +1372,7 @@ __global__ void __launch_bounds__(256) paper_kernel(PaperLaunch L) {
                 __builtin_nontemporal_store(narrow<DTYPE>(xv), row + c);
                 __builtin_nontemporal_store(narrow<DTYPE>(yv), row + c + 1);
             } else {
-                __builtin_nontemporal_store(value1<DIST, DTYPE, G>(ea.step_rot(kr), inv_rate), row + c);
+                __builtin_nontemporal_store(value1<DIST, DTYPE, G>(ea.step_rot(kr), half_inv_rate), row + c);
             }
         }
         if (L.n_cb > 1) break;  // a column block covers one row
