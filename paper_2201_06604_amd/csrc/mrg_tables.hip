@@ -3,12 +3,12 @@
 // table, entries drawn in row-major order by inversion of their conditional
 // hypergeometric distributions, one uniform per free entry.
 //
-// Each entry is sampled by hyper_invert_ck (mrg_hyper.h): the inversion that
-// the oracle defines, with two shortcuts that give the same bits; the
-// checkpoints of its search live in LDS.
+// Each entry is sampled by hyper_search (mrg_hyper.h), or by the definition
+// itself, hyper_invert, where the search's bounds do not decide.
 //
-// One lane owns one table.  The loops' trip counts depend on the margins, so
-// lanes of a wave diverge; that is the price of exact inversion.
+// One lane owns one table.  Trip counts depend on the margins, so lanes of a
+// wave diverge; both kernels therefore run one flat loop over a table's
+// entries, and what a lane indexes by column lives in LDS.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -22,155 +22,263 @@
 
 namespace mrg355 {
 
-// Inversion checkpoints per lane (LDS, 20 bytes each).  More shorten the
-// second pass of a wide search but hold LDS that would otherwise let more
-// blocks run: 10^6 tables of totals 5..200 took 2.27 / 2.25 / 2.12 / 2.06 /
-// 2.39 ms with 3 / 4 / 5 / 6 / 8 (6: five blocks per CU); the paper's Fisher
-// tables (totals about 12,900) 41.4 / 38.8 / 45.9 / 43.7 ms (Table 1) with
-// 6 / 8 / 12 / 16.
-#ifndef MRG_TABLE_CK
-#define MRG_TABLE_CK 6
-#endif
-#ifndef MRG_FISHER_CK
-#define MRG_FISHER_CK 8
-#endif
-constexpr int kTablesCk = MRG_TABLE_CK;
-constexpr int kFisherCk = MRG_FISHER_CK;
 constexpr int kTableBlock = 256;
+constexpr float kTableOverhead = 20.0f;  // of an inversion, in units of a total's square root
 
 // log(n!) for n <= kTableMaxTotal: lgamma(n+1) in long double on the host,
 // rounded to double, uploaded once per device (ensure_logfact).  Every entry
 // of a valid table is at most its grand total, so the index is in range.
 __device__ double g_logfact[kTableMaxTotal + 1];
 
-__device__ __forceinline__ double log_factorial(int n) { return g_logfact[n]; }
+struct LogFactGlobal {
+    __device__ __forceinline__ double operator()(int k) const { return g_logfact[k]; }
+};
 
-// One I x J table (I, J <= MAXD) with row totals r[], column totals c[]:
-// entries to tab[i*ld + j] (when tab is not null); returns -sum log(n_ij!)
-// summed row-major.  The engine advances (I-1)(J-1) steps.
-template <int MAXD, int NCK, typename Engine>
-__device__ double sample_table(Engine& e, double norm, int I, int J, const int32_t* r, const int32_t* c, int32_t* tab,
-                               int ld, HyperCk ck) {
+// The first kLdsFact of them in LDS, for tables whose grand total is below it.
+// A lane's arguments are its own, so a read of the global table takes the
+// address unit a cycle per lane (64 a wave, nine reads an inversion), an LDS
+// read about four.
+constexpr int kLdsFact = 1024;
+struct LogFactLds {
+    const double* tab;
+    __device__ __forceinline__ double operator()(int k) const { return tab[k]; }
+};
+
+// One I x J table of grand total `total` with row totals row(i) and column
+// totals col(j), which are used up: take(i, j, x) receives every entry in
+// row-major order.  Returns -sum log(n_ij!) summed in that order.  The engine
+// advances (I-1)(J-1) steps.
+//
+// One loop over the entries, the row's end handled inside it: with a loop over
+// rows around a loop over columns a wave of mixed shapes ran the product of
+// the largest row and column counts among its lanes.
+template <typename Engine, typename LogFact, typename Row, typename Col, typename Take>
+__device__ __forceinline__ double sample_table(Engine& e, double norm, LogFact lf, int total, int I, int J, Row row,
+                                               Col col, Take take) {
     const typename Engine::Regs kr;
-    int32_t crem[MAXD];
-    for (int j = 0; j < J; ++j) crem[j] = c[j];
     double stat = 0.0;
-    for (int i = 0; i < I - 1; ++i) {
-        int64_t rrem = r[i];
-        int64_t Np = 0;  // units left in columns j..J-1 over rows i..I-1
-        for (int j = 0; j < J; ++j) Np += crem[j];
-        for (int j = 0; j < J - 1; ++j) {
-            const double u = to_f64(e.step_rot(kr)) * norm;
-            const int x = hyper_invert_ck<NCK>(u, Np, crem[j], rrem, ck);
-            if (tab) tab[i * ld + j] = x;
-            stat -= log_factorial(x);
-            rrem -= x;
-            Np -= crem[j];
-            crem[j] -= x;
+    int i = 0, j = 0;
+    int left = total;  // units left in rows i..I-1
+    int n = I > 1 ? row(0) : 0, Np = left;
+    double lfN = lf(Np);
+    // determined entries: the row's last is what the row has left
+    auto row_end = [&]() {
+        take(i, J - 1, n);
+        stat -= lf(n);
+        col(J - 1) -= n;
+        left -= row(i);
+        ++i;
+        j = 0;
+        n = row(i);
+        Np = left;
+    };
+    if (J == 1)
+        while (i < I - 1) row_end();
+    const int entries = (I - 1) * (J - 1);
+    for (int k = 0; k < entries; ++k) {
+        const double u = to_f64(e.step_rot(kr)) * norm;
+        const int K = col(j);
+        int x = hyper_search(u, Np, K, n, lfN, lf);
+        if (x < 0) x = hyper_invert(u, Np, K, n);
+        take(i, j, x);
+        stat -= lf(x);
+        n -= x;
+        Np -= K;
+        col(j) = K - x;
+        if (++j == J - 1) {
+            row_end();
+            lfN = lf(Np);
         }
-        if (tab) tab[i * ld + J - 1] = static_cast<int32_t>(rrem);  // determined by the row total
-        stat -= log_factorial(static_cast<int>(rrem));
-        crem[J - 1] -= static_cast<int32_t>(rrem);
     }
-    for (int j = 0; j < J; ++j) {  // the last row is what the columns have left
-        if (tab) tab[(I - 1) * ld + j] = crem[j];
-        stat -= log_factorial(crem[j]);
+    for (int c = 0; c < J; ++c) {  // the last row is what the columns have left
+        const int x = col(c);
+        take(I - 1, c, x);
+        stat -= lf(x);
     }
     return stat;
 }
 
-// The engine and the scale 1/(m1+1) of generator G.
+// The scale 1/(m1+1) of generator G.
 template <int G>
-struct GenOf {
-    using Engine = F64EngineOf<G>;
-    static constexpr double norm = G == kGen32k3a ? kNorm : kNorm31;
+__device__ __forceinline__ constexpr double norm_of() {
+    return G == kGen32k3a ? kNorm : kNorm31;
+}
+
+// Tables of shape I[t] x J[t] (<= 5 x 5) with margins rows[t][5], cols[t][5],
+// table t from stream t; outputs tabs[t][5][5] (zero padded) and stats[t]
+// (optional).  A table whose shape is out of range or whose margins are
+// negative, differ in total or total more than kTableMaxTotal gets zeros and a
+// NaN statistic, and its stream is left as it was (the checks also bound every
+// loop).
+struct TablesArgs {
+    uint32_t* streams;
+    uint64_t n;
+    const int32_t *I, *J, *rows, *cols;
+    int32_t* tabs;
+    double* stats;
+    uint32_t window;  // tables per block: kTableBlock or kTableWindow
 };
 
-// Table t: shape I[t] x J[t] (<= 5 x 5), margins rows[t][5], cols[t][5],
-// from stream t; outputs tabs[t][5][5] (zero padded) and stats[t] (optional).
-// A table whose shape is out of range or whose margins are negative, differ
-// in total or total more than kTableMaxTotal gets zeros and a NaN statistic,
-// and its stream is left as it was (the checks also bound every loop).
-template <int G>
-__device__ __forceinline__ void one_table(uint64_t t, uint32_t* streams, const int32_t* I, const int32_t* J,
-                                          const int32_t* rows, const int32_t* cols, int32_t* tabs, double* stats,
-                                          const HyperCk& ck) {
-    int32_t* out = tabs + t * 25;
-#pragma unroll
-    for (int k = 0; k < 25; ++k) out[k] = 0;
-    const int It = I[t], Jt = J[t];
-    bool ok = It >= 1 && It <= 5 && Jt >= 1 && Jt <= 5;
+constexpr int kTabWords = 25;
+constexpr uint32_t kTableWindow = 2 * kTableBlock;
+constexpr int kBuckets = 64;
+
+// The grand total of a table whose shape and margins are valid, else -1.
+template <typename T>
+__device__ __forceinline__ int checked_total(int I, int J, const T* row, const T* col) {
+    if (!(I >= 1 && I <= 5 && J >= 1 && J <= 5)) return -1;
     int64_t rs = 0, cs = 0;
-    for (int k = 0; ok && k < It; ++k) {
-        ok = rows[t * 5 + k] >= 0;
-        rs += rows[t * 5 + k];
+    bool ok = true;
+    for (int i = 0; i < I; ++i) {
+        ok = ok && row[i] >= 0;
+        rs += row[i];
     }
-    for (int k = 0; ok && k < Jt; ++k) {
-        ok = cols[t * 5 + k] >= 0;
-        cs += cols[t * 5 + k];
+    for (int j = 0; j < J; ++j) {
+        ok = ok && col[j] >= 0;
+        cs += col[j];
     }
-    ok = ok && rs == cs && rs <= kTableMaxTotal;
-    if (!ok) {
-        if (stats) stats[t] = __builtin_nan("");
-        return;
-    }
-    uint32_t* rec = streams + t * 18;
+    return ok && rs == cs && rs <= kTableMaxTotal ? static_cast<int>(rs) : -1;
+}
+
+// Table t of valid total `total`: entries through take(i, j, x).
+template <int G, typename LogFact, typename Row, typename Col, typename Take>
+__device__ __forceinline__ double one_table(const TablesArgs& a, uint64_t t, int total, LogFact lf, Row row, Col col,
+                                            Take take) {
+    uint32_t* rec = a.streams + t * 18;
     uint32_t x[6];
 #pragma unroll
     for (int w = 0; w < 6; ++w) x[w] = rec[w];
-    typename GenOf<G>::Engine e;
+    F64EngineOf<G> e;
     e.load(x);
-    const double stat = sample_table<5, kTablesCk>(e, GenOf<G>::norm, It, Jt, rows + t * 5, cols + t * 5, out, 5, ck);
-    if (stats) stats[t] = stat;
+    const double stat = sample_table(e, norm_of<G>(), lf, total, a.I[t], a.J[t], row, col, take);
     e.save(x);
 #pragma unroll
     for (int w = 0; w < 6; ++w) rec[w] = x[w];
+    return stat;
 }
 
-// A block takes 256 consecutive tables.  A table makes (I-1)(J-1)
-// inversions, 1 to 16, each searching a range that grows like the square
-// root of the table's total, and a wave runs as long as its longest lane;
-// so the block first orders its tables by the estimate (I-1)(J-1) sqrt(total)
+// A block takes a window of consecutive tables.  A table makes (I-1)(J-1)
+// inversions, 1 to 16, each over a range that grows like the square root of the
+// table's total, and a wave runs as long as its longest lane; so the block first
+// orders its tables by the estimate (I-1)(J-1) (kTableOverhead + sqrt(total))
 // in 64 buckets (a counting sort in LDS: the order within a bucket does not
-// matter, every table has its own stream and output), and each wave then
-// takes 64 tables of about the same work (10^6 tables of the 2x2..5x5 mix:
-// 2.62 -> 2.40 ms).  Sorting windows of 3 or 7 blocks' tables, taken in
-// rounds by fewer blocks, were no faster or slower.
+// matter, every table has its own stream and output), and its waves then take
+// groups of 64 neighbours in that order, longest first, until none is left: with
+// one group a wave, the waves of the short tables left their place empty until
+// the block's longest was done.
+//
+// Where all margins of the window are below kLdsFact and so is every total,
+// everything an inversion reads lies in LDS: margins (read from global memory in
+// whole lines; a lane's own lie 20 bytes from its neighbour's), logarithms, and
+// a group's entries, written out as whole tables.  Any other window reads its
+// margins and logarithms and writes its entries where they are.
+//
+// Bound by VALU issue (68% busy) and by lanes that wait for the longest search
+// of their wave (68% of lanes active).  10^6 tables of the 2x2..5x5 mix of
+// totals 5..200: 1648 us with two passes over each range and divisions, 363
+// with the search, 205 with one loop over the entries, 185 with logarithms in
+// LDS, 181 with groups taken longest first.  Four waves a SIMD (128 registers,
+// 12 bytes of the general case spilled) against three: 181 against 203 us.
 template <int G>
-__global__ void __launch_bounds__(kTableBlock) tables_kernel(uint32_t* streams, uint64_t n, const int32_t* I,
-                                                             const int32_t* J, const int32_t* rows, const int32_t* cols,
-                                                             int32_t* tabs, double* stats) {
-    __shared__ double ck_s[kTablesCk * kTableBlock], ck_w[kTablesCk * kTableBlock];
-    __shared__ int ck_r[kTablesCk * kTableBlock];
-    constexpr int kBuckets = 64;
-    __shared__ uint16_t order[kTableBlock];
+__global__ void __launch_bounds__(kTableBlock) __attribute__((amdgpu_waves_per_eu(4)))
+tables_kernel(TablesArgs a) {
+    constexpr int kWaves = kTableBlock / 64;
+    __shared__ double fact_lds[kLdsFact];
+    __shared__ uint16_t row_lds[kTableWindow * 5], col_lds[kTableWindow * 5];
+    __shared__ uint32_t tab_lds[kWaves][64 * kTabWords / 2];  // 16-bit entries; 5 column totals a lane in the other case
+    __shared__ uint16_t order[kTableWindow];
     __shared__ uint32_t start[kBuckets + 1];
-    const HyperCk ck{ck_s + threadIdx.x, ck_w + threadIdx.x, ck_r + threadIdx.x, kTableBlock};
-    const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kTableBlock;
-    const uint32_t here = n - base < kTableBlock ? static_cast<uint32_t>(n - base) : kTableBlock;
-    // bucket of the work estimate (0 for shapes out of range: they stop at once)
-    auto key_of = [&](uint32_t k) {
+    __shared__ uint32_t next_group;
+    const uint64_t base = static_cast<uint64_t>(blockIdx.x) * a.window;
+    const uint32_t here = a.n - base < a.window ? static_cast<uint32_t>(a.n - base) : a.window;
+    const uint32_t me = threadIdx.x, lane = me & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(me >> 6);
+    uint32_t high = 0;  // 16 bits and more of any margin (negative ones too)
+    for (uint32_t k = me; k < here * 5; k += kTableBlock) {
+        const uint32_t r = static_cast<uint32_t>(a.rows[base * 5 + k]), c = static_cast<uint32_t>(a.cols[base * 5 + k]);
+        high |= (r | c) >> 15;
+        row_lds[k] = static_cast<uint16_t>(r);
+        col_lds[k] = static_cast<uint16_t>(c);
+    }
+    if (me <= kBuckets) start[me] = 0;
+    if (me == 0) next_group = 0;
+    bool small = __syncthreads_or(static_cast<int>(high)) == 0;
+    uint32_t key[kTableWindow / kTableBlock];  // buckets of this thread's tables (0 for those refused: they stop at once)
+    int most = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kTableWindow / kTableBlock; ++q) {
+        const uint32_t k = me + q * kTableBlock;
+        key[q] = 0;
+        if (k >= here) continue;
         const uint64_t t = base + k;
-        const int It = I[t], Jt = J[t];
-        if (!(It >= 1 && It <= 5 && Jt >= 1 && Jt <= 5)) return 0u;
-        int64_t total = 0;
-        for (int r = 0; r < It; ++r) total += rows[t * 5 + r];
-        const double est = (It - 1) * (Jt - 1) * __builtin_sqrt(static_cast<double>(total > 0 ? total : 0));
-        const double b = est * 0.125;  // 16 inversions at a total of 1,000 reach bucket 63
-        return b >= kBuckets - 1 ? static_cast<uint32_t>(kBuckets - 1) : static_cast<uint32_t>(b);
-    };
-    if (threadIdx.x <= kBuckets) start[threadIdx.x] = 0;
-    __syncthreads();
-    const uint32_t k = threadIdx.x;
-    const uint32_t key = k < here ? key_of(k) : 0u;
-    if (k < here) atomicAdd(&start[key + 1], 1u);
-    __syncthreads();
-    if (threadIdx.x == 0)
+        const int It = a.I[t], Jt = a.J[t];
+        const int total = small ? checked_total(It, Jt, row_lds + k * 5, col_lds + k * 5)
+                                : checked_total(It, Jt, a.rows + t * 5, a.cols + t * 5);
+        most = total > most ? total : most;
+        if (total >= 0) {
+            const float est = static_cast<float>((It - 1) * (Jt - 1)) *
+                              (kTableOverhead + __builtin_sqrtf(static_cast<float>(total)));
+            key[q] = static_cast<uint32_t>(fminf(est * (1.0f / 16.0f), kBuckets - 1.0f));
+        }
+        key[q] = kBuckets - 1 - key[q];  // longest first
+        atomicAdd(&start[key[q] + 1], 1u);
+    }
+    small = __syncthreads_or(most >= kLdsFact) == 0 && small;
+    if (me == 0)
         for (int c = 1; c <= kBuckets; ++c) start[c] += start[c - 1];  // start[c] = tables in buckets below c
+    if (small)
+        for (uint32_t k = me; k < kLdsFact; k += kTableBlock) fact_lds[k] = g_logfact[k];
+    else
+        for (uint32_t k = me; k < here * kTabWords; k += kTableBlock) a.tabs[base * kTabWords + k] = 0;
+    __syncthreads();  // orders the zeros before the entries too
+#pragma unroll
+    for (uint32_t q = 0; q < kTableWindow / kTableBlock; ++q) {
+        const uint32_t k = me + q * kTableBlock;
+        if (k < here) order[atomicAdd(&start[key[q]], 1u)] = static_cast<uint16_t>(k);
+    }
     __syncthreads();
-    if (k < here) order[atomicAdd(&start[key], 1u)] = static_cast<uint16_t>(k);
-    __syncthreads();
-    if (k < here) one_table<G>(base + order[k], streams, I, J, rows, cols, tabs, stats, ck);
+    for (;;) {  // every lane executes the atomic, with 1 on lane 0 only: wave-uniform
+        const uint32_t g = __builtin_amdgcn_readfirstlane(atomicAdd(&next_group, lane == 0 ? 1u : 0u));
+        if (g * 64 >= here) break;
+        const uint32_t in_group = here - g * 64 < 64 ? here - g * 64 : 64;
+        const uint32_t k = lane < in_group ? order[g * 64 + lane] : 0;
+        const uint64_t t = base + k;
+        double stat = __builtin_nan("");
+        if (small) {
+            uint32_t* words = tab_lds[wave];
+            for (uint32_t w = lane; w < 64 * kTabWords / 2; w += 64) words[w] = 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            uint16_t* tabs16 = reinterpret_cast<uint16_t*>(words);
+            if (lane < in_group) {
+                const uint16_t* row = row_lds + k * 5;
+                uint16_t* col = col_lds + k * 5;
+                uint16_t* out = tabs16 + lane * kTabWords;
+                const int total = checked_total(a.I[t], a.J[t], row, col);
+                if (total >= 0)
+                    stat = one_table<G>(
+                        a, t, total, LogFactLds{fact_lds}, [=](int i) { return static_cast<int>(row[i]); },
+                        [=](int j) -> uint16_t& { return col[j]; },
+                        [=](int i, int j, int x) { out[i * 5 + j] = static_cast<uint16_t>(x); });
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (uint32_t w = lane; w < in_group * kTabWords; w += 64) {
+                const uint32_t l = w / kTabWords;
+                a.tabs[(base + order[g * 64 + l]) * kTabWords + (w - l * kTabWords)] = tabs16[w];
+            }
+        } else if (lane < in_group) {
+            int32_t* col = reinterpret_cast<int32_t*>(tab_lds[wave]) + lane * 5;
+            const int32_t *row = a.rows + t * 5, *c = a.cols + t * 5;
+            int32_t* out = a.tabs + t * kTabWords;
+            const int total = checked_total(a.I[t], a.J[t], row, c);
+            if (total >= 0) {
+                for (int j = 0; j < a.J[t]; ++j) col[j] = c[j];
+                stat = one_table<G>(
+                    a, t, total, LogFactGlobal{}, [=](int i) { return row[i]; }, [=](int j) -> int32_t& { return col[j]; },
+                    [=](int i, int j, int x) { out[i * 5 + j] = x; });
+            }
+        }
+        if (a.stats && lane < in_group) a.stats[t] = stat;
+    }
 }
 
 // The count is cleared by a kernel, not a memset, so the launch can be
@@ -189,24 +297,33 @@ struct FisherArgs {
 
 // Replicate b < B of the observed table's margins from stream b; counts the
 // replicates whose statistic is <= threshold (one atomic per wave; every
-// lane executes it, with the wave's count on lane 0 and 0 elsewhere).
+// lane executes it, with the wave's count on lane 0 and 0 elsewhere).  Column
+// totals lie in LDS (as registers they cost 32 of them and a wave a SIMD).
+// Bound by VALU issue, 92% busy at 666 instructions an entry of a wave, three
+// quarters of them the search's loop: 12 x 12 of 12,912 counts, 2^20 replicates,
+// 29.9 -> 2.35 ms.
 template <int G>
 __global__ void __launch_bounds__(kTableBlock) fisher_kernel(FisherArgs a) {
-    __shared__ double ck_s[kFisherCk * kTableBlock], ck_w[kFisherCk * kTableBlock];
-    __shared__ int ck_r[kFisherCk * kTableBlock];
-    const HyperCk ck{ck_s + threadIdx.x, ck_w + threadIdx.x, ck_r + threadIdx.x, kTableBlock};
+    extern __shared__ int32_t fisher_cols[];  // a.J * kTableBlock
     const uint64_t b = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     const uint32_t lane = threadIdx.x & 63;
     bool hit = false;
     if (b < a.B) {
+        int32_t* col = fisher_cols + threadIdx.x;  // column j's remaining total at col[j * kTableBlock]
+        int total = 0;
+        for (int j = 0; j < a.J; ++j) {
+            col[j * kTableBlock] = a.c[j];
+            total += a.c[j];
+        }
         uint32_t* rec = a.streams + b * 18;
         uint32_t x[6];
 #pragma unroll
         for (int w = 0; w < 6; ++w) x[w] = rec[w];
-        typename GenOf<G>::Engine e;
+        F64EngineOf<G> e;
         e.load(x);
-        const double stat =
-            sample_table<kFisherMaxDim, kFisherCk>(e, GenOf<G>::norm, a.I, a.J, a.r, a.c, nullptr, 0, ck);
+        const double stat = sample_table(e, norm_of<G>(), LogFactGlobal{}, total, a.I, a.J, [&](int i) { return a.r[i]; },
+                                         [=](int j) -> int32_t& { return col[j * kTableBlock]; },
+                                         [](int, int, int) {});
         hit = stat <= a.threshold;
         if (a.stats) a.stats[b] = stat;
         e.save(x);
@@ -249,13 +366,13 @@ hipError_t ensure_logfact() {
 hipError_t launch_tables(int gen, uint32_t* streams, uint64_t n, const int32_t* I, const int32_t* J,
                          const int32_t* rows, const int32_t* cols, int32_t* tabs, double* stats, hipStream_t s) {
     if (hipError_t e = ensure_logfact()) return e;
-    const dim3 grid(static_cast<unsigned>((n + kTableBlock - 1) / kTableBlock));
-    if (gen == kGen32k3a)
-        hipLaunchKernelGGL(tables_kernel<kGen32k3a>, grid, dim3(kTableBlock), 0, s, streams, n, I, J, rows, cols, tabs,
-                           stats);
-    else
-        hipLaunchKernelGGL(tables_kernel<kGen31k3p>, grid, dim3(kTableBlock), 0, s, streams, n, I, J, rows, cols, tabs,
-                           stats);
+    // windows of two groups a wave once they fill the chip (about four blocks a
+    // CU), of one below that
+    TablesArgs a{streams, n, I, J, rows, cols, tabs, stats, kTableBlock};
+    if (n >= kTableWindow * 1024ull) a.window = kTableWindow;
+    const dim3 grid(static_cast<unsigned>((n + a.window - 1) / a.window));
+    if (gen == kGen32k3a) hipLaunchKernelGGL(tables_kernel<kGen32k3a>, grid, dim3(kTableBlock), 0, s, a);
+    else hipLaunchKernelGGL(tables_kernel<kGen31k3p>, grid, dim3(kTableBlock), 0, s, a);
     return hipGetLastError();
 }
 
@@ -280,8 +397,9 @@ hipError_t launch_fisher(int gen, uint32_t* streams, uint64_t B, int I, int J, c
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || B == 0) return e;
     const dim3 grid(static_cast<unsigned>((B + kTableBlock - 1) / kTableBlock));
-    if (gen == kGen32k3a) hipLaunchKernelGGL(fisher_kernel<kGen32k3a>, grid, dim3(kTableBlock), 0, s, a);
-    else hipLaunchKernelGGL(fisher_kernel<kGen31k3p>, grid, dim3(kTableBlock), 0, s, a);
+    const size_t lds = static_cast<size_t>(J) * kTableBlock * sizeof(int32_t);  // J <= 32: 32 KB at most
+    if (gen == kGen32k3a) hipLaunchKernelGGL(fisher_kernel<kGen32k3a>, grid, dim3(kTableBlock), lds, s, a);
+    else hipLaunchKernelGGL(fisher_kernel<kGen31k3p>, grid, dim3(kTableBlock), lds, s, a);
     return hipGetLastError();
 }
 
