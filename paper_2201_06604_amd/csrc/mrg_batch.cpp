@@ -34,9 +34,10 @@ struct mrg_batch_plan {
     uint32_t gang;  // 1 = class queues of wave tiles; 2, 4, 8 = gangs of that many waves
     std::vector<BatchReq> reqs;
     std::vector<BatchTile> tiles;
+    size_t cut;  // tiles of the cut; in gang mode, each class's padded to whole gangs
     uint32_t tile_lo[kClasses + 1];
     double cls_cost[kClasses];
-    uint32_t n_gangs;  // gang mode: tiles holds n_gangs * gang entries (padding: req = kNoRequest)
+    uint32_t n_gangs;
     uint32_t narrow;   // every request runs one stream per lane (the narrow gang kernel serves it)
     uint32_t xq_lo[kXcdQueues + 1];  // gang mode: the gangs of each XCD's queue
     std::vector<uint32_t> fin_req;
@@ -48,10 +49,8 @@ struct mrg_batch_plan {
 
 namespace {
 
-// The shape the autotuner picks for the 4,096-request mix of lengths 10^3 to
-// 10^7 and 64 to 1,024 streams: gangs of 8 waves, one stream per lane (the
-// narrow kernel), 256-unit tiles, 4 waves per SIMD.
-constexpr uint32_t kDefaultTileUnits = 256;
+// Automatic shape: gangs of 8 waves, one stream per lane (the narrow kernel), 4
+// waves per SIMD.
 constexpr uint32_t kDefaultWavesPerSimd = 4;
 constexpr uint32_t kDefaultGang = 8;
 constexpr unsigned kBatchBlock = 256;
@@ -76,6 +75,29 @@ double unit_cost(int dist, int dtype) {
         case kExponential: return 1.0 / 300.0;
         default: return dtype == kF64 ? 1.0 / 700.0 : 1.0 / 1400.0;
     }
+}
+
+// Automatic tile length.  A tile jumps to its first draw and is counted off at
+// its end, so long ones cost less in all; but a batch lasts at least as long as
+// its last gangs, and one of few requests needs short ones to reach every CU.
+// The best length grows like the square root of the work, counted in units of
+// one wave: mixes of lengths 10^3 up to 10^6 and 10^7 took, by tile length,
+//   64 requests to 10^6 (1.5 10^5 units)    32: 70 us, 64: 80, 256: 200
+//   256 to 10^6 (6 10^5)                    32: 143, 64: 142, 128: 158, 256: 229
+//   1,024 to 10^6 (2.3 10^6)                64: 363, 96: 346, 128: 364, 256: 427
+//   256 to 10^7 (4.3 10^6)                  64: 462, 128: 436, 256: 488
+//   1,024 to 10^7 (1.7 10^7)                128: 1569, 192: 1515, 256: 1524, 384: 1560
+//   4,096 to 10^7 (6.9 10^7)                192: 6370, 256: 6240, 384: 6170, 768: 6250
+// Multiples of 32 keep the jumps to few digits.
+uint32_t automatic_tile_units(const std::vector<mrg355::PlanReq>& user) {
+    double units = 0.0;
+    for (const mrg355::PlanReq& u : user) {
+        if (u.q.n == 0) continue;
+        const double draws = static_cast<double>(u.q.n) / u.q.n_streams;
+        units += (u.q.dist == MRG_NORMAL ? draws / 2 : draws) * std::ceil(u.q.n_streams / 64.0);
+    }
+    const double t = std::sqrt(units) / (18.0 * 32.0) + 0.5;
+    return 32 * static_cast<uint32_t>(std::min(12.0, std::max(1.0, t)));
 }
 
 mrg_status validate_request(const mrg_request& q, size_t i) {
@@ -124,14 +146,26 @@ void pack_tables(mrg_batch_plan& P) {
     put(P.off_fin_pre, P.fin_pre.data(), P.fin_pre.size() * sizeof(uint64_t));
 }
 
-// Gang mode: within each class, tiles longest first and, among tiles of equal
-// length, in (request, chunk, stream block) order, so that a gang -- G
-// consecutive tiles -- holds neighbouring stream blocks of one request and
-// chunk wherever the request has them; the last gang of a class is padded.
-// The classes' gangs are then merged into one queue by the share of their
-// class's estimated work done at each gang's midpoint, so that every class
-// advances at the same pace and all of them finish together.
+// Gang mode: a gang holds whole rows.  The tiles of one request and chunk (its
+// stream blocks) stay together: up to G of them take a wave each; in a narrow
+// plan up to 2G take half as many waves, wave w the blocks w and w + D of D
+// waves (BatchTile.gap); more are cut into equal column groups of that size.  A
+// gang that has waves left takes another group of the same class that fits them
+// (of at least 7/8 of its length, so that no wave waits long), else they stay
+// idle.  A row that two gangs share ends and begins within a 128-byte line
+// unless its start happens to be aligned, and the two halves of that line reach
+// memory from different L2s or at different times, as partial writes: with gangs
+// filled to the last wave (one row in most gangs cut in two) stores alone took
+// 7.4 ms for the 4,096-request mix, with rows cut only above 512 streams 6.2 ms,
+// with whole rows 4.8 ms, and 4.8 ms where every row starts on a line.
+//
+// Within each class, tiles go longest first and, among tiles of equal length,
+// in (request, chunk, stream block) order.  The classes' gangs are then merged
+// into one queue by the share of their class's estimated work done at each
+// gang's midpoint, so that every class advances at the same pace and all of
+// them finish together.
 void order_gangs(mrg_batch_plan& P, const std::vector<double>& cost, const std::vector<uint64_t>& len) {
+    constexpr uint32_t kNone = 0xffffffffu;
     const uint32_t G = P.gang;
     std::vector<uint32_t> by_cls[kClasses];
     for (uint32_t t = 0; t < P.tiles.size(); ++t)
@@ -139,34 +173,62 @@ void order_gangs(mrg_batch_plan& P, const std::vector<double>& cost, const std::
     struct Gang {
         double key;
         int cls;
-        uint32_t first;  // index into `member`
+        uint32_t first;  // its G places in `member`
+        uint32_t used;   // and how many of them hold a tile
         double cost;
         uint32_t req;    // the request of its first tile
+        uint64_t len;    // of its longest tile
     };
     std::vector<Gang> gangs;
-    std::vector<uint32_t> member;  // tile indices, G per gang, kNoRequest for padding
+    std::vector<BatchTile> member;
     for (int c = 0; c < kClasses; ++c) {
         std::vector<uint32_t>& v = by_cls[c];
         std::stable_sort(v.begin(), v.end(), [&](uint32_t a, uint32_t b) { return len[a] > len[b]; });
-        const size_t n_g = (v.size() + G - 1) / G;
-        std::vector<double> gcost(n_g, 0.0);
-        double total = 0.0;
-        for (size_t g = 0; g < n_g; ++g) {
-            for (uint32_t w = 0; w < G; ++w) {
-                const size_t k = g * G + w;
-                if (k < v.size()) gcost[g] = std::max(gcost[g], cost[v[k]]);
+        const size_t first_gang = gangs.size();
+        std::vector<std::vector<uint32_t>> open(G);  // gangs of this class by waves left (1..G-1)
+        std::vector<BatchTile> group;
+        for (size_t k = 0; k < v.size();) {
+            const BatchTile& head = P.tiles[v[k]];
+            size_t e = k;
+            while (e < v.size() && P.tiles[v[e]].req == head.req && P.tiles[v[e]].chunk == head.chunk) ++e;
+            const uint32_t nb = static_cast<uint32_t>(e - k), most = P.narrow ? 2 * G : G;
+            const uint32_t parts = (nb + most - 1) / most, per = (nb + parts - 1) / parts;
+            for (uint32_t lo = 0; lo < nb; lo += per) {
+                const uint32_t here = std::min(per, nb - lo);
+                const uint32_t waves = here <= G ? here : (here + 1) / 2;
+                group.clear();
+                for (uint32_t w = 0; w < waves; ++w) {
+                    BatchTile t = P.tiles[v[k + lo + w]];
+                    if (w + waves < here) t.at |= waves << kTileGapBit;
+                    group.push_back(t);
+                }
+                const uint64_t l = len[v[k]];
+                uint32_t to = kNone;
+                for (uint32_t left = waves; left < G && to == kNone; ++left)
+                    if (!open[left].empty() && gangs[open[left].back()].len * 7 <= l * 8) {
+                        to = open[left].back();
+                        open[left].pop_back();
+                    }
+                if (to == kNone) {
+                    to = static_cast<uint32_t>(gangs.size());
+                    gangs.push_back(Gang{0.0, c, static_cast<uint32_t>(member.size()), 0, 0.0, head.req, l});
+                    member.resize(member.size() + G);
+                }
+                Gang& g = gangs[to];
+                for (const BatchTile& t : group) {
+                    member[g.first + g.used++] = t;
+                    g.cost = std::max(g.cost, cost[v[k]] * (t.at >> kTileGapBit ? 2.0 : 1.0));
+                }
+                P.reqs[head.req].n_tiles -= here - waves;
+                if (g.used < G) open[G - g.used].push_back(to);
             }
-            total += gcost[g];
+            k = e;
         }
-        double done = 0.0;
-        for (size_t g = 0; g < n_g; ++g) {
-            gangs.push_back(Gang{total > 0 ? (done + 0.5 * gcost[g]) / total : 0.0, c,
-                                 static_cast<uint32_t>(member.size()), gcost[g], P.tiles[v[g * G]].req});
-            done += gcost[g];
-            for (uint32_t w = 0; w < G; ++w) {
-                const size_t k = g * G + w;
-                member.push_back(k < v.size() ? v[k] : kNoRequest);
-            }
+        double total = 0.0, done = 0.0;
+        for (size_t g = first_gang; g < gangs.size(); ++g) total += gangs[g].cost;
+        for (size_t g = first_gang; g < gangs.size(); ++g) {
+            gangs[g].key = total > 0 ? (done + 0.5 * gangs[g].cost) / total : 0.0;
+            done += gangs[g].cost;
         }
     }
     std::stable_sort(gangs.begin(), gangs.end(), [](const Gang& a, const Gang& b) {
@@ -191,20 +253,20 @@ void order_gangs(mrg_batch_plan& P, const std::vector<double>& cost, const std::
         load[best] += req_cost[r];
     }
     std::vector<BatchTile> out;
-    out.reserve(gangs.size() * G);
+    std::vector<uint32_t> lo;  // the first tile of each gang
+    out.reserve(member.size());
     P.xq_lo[0] = 0;
     for (int x = 0; x < kXcdQueues; ++x) {
         uint32_t n = 0;
         for (const Gang& g : gangs) {
             if (xcd_of[g.req] != x) continue;
             ++n;
-            for (uint32_t w = 0; w < G; ++w) {
-                const uint32_t t = member[g.first + w];
-                out.push_back(t == kNoRequest ? BatchTile{kNoRequest, 0, 0, 0} : P.tiles[t]);
-            }
+            lo.push_back(static_cast<uint32_t>(out.size()));
+            out.insert(out.end(), member.begin() + g.first, member.begin() + g.first + g.used);
         }
         P.xq_lo[x + 1] = P.xq_lo[x] + n;
     }
+    for (size_t g = 0; g < lo.size(); ++g) out[g].gang_lo = lo[g];  // every gang has a tile
     P.tiles.swap(out);
     P.n_gangs = static_cast<uint32_t>(gangs.size());
     for (int c = 0; c <= kClasses; ++c) P.tile_lo[c] = 0;
@@ -297,7 +359,13 @@ mrg_status build(mrg_batch_plan& P) {
         }
         P.reqs.push_back(R);
     }
+    P.narrow = 1;
+    for (const BatchReq& R : P.reqs) P.narrow &= batch_kind_narrow(static_cast<int>(R.kind)) ? 1u : 0u;
     P.n_gangs = 0;
+    size_t in_class[kClasses] = {};
+    for (const BatchTile& t : P.tiles) ++in_class[batch_kind_class(static_cast<int>(P.reqs[t.req].kind))];
+    P.cut = 0;
+    for (size_t c : in_class) P.cut += (c + P.gang - 1) / P.gang * P.gang;
     if (P.gang > 1) {
         order_gangs(P, cost, len);
     } else {
@@ -323,14 +391,12 @@ mrg_status build(mrg_batch_plan& P) {
     P.tiles.swap(sorted);
     }
     P.fin_total = P.fin_pre.back();
-    P.narrow = 1;
-    for (const BatchReq& R : P.reqs) P.narrow &= batch_kind_narrow(static_cast<int>(R.kind)) ? 1u : 0u;
     // workspace layout
     const size_t n_req = P.reqs.size();
     P.off_slots = 256;
     P.off_reqs = align_up(P.off_slots + n_req * sizeof(BatchSlot), 256);
     P.off_tiles = align_up(P.off_reqs + n_req * sizeof(BatchReq), 256);
-    P.off_fin_req = align_up(P.off_tiles + P.tiles.size() * sizeof(BatchTile), 256);
+    P.off_fin_req = align_up(P.off_tiles + (P.gang > 1 ? P.cut : P.tiles.size()) * sizeof(BatchTile), 256);
     P.off_fin_pre = align_up(P.off_fin_req + P.fin_req.size() * sizeof(uint32_t), 256);
     P.bytes = align_up(P.off_fin_pre + P.fin_pre.size() * sizeof(uint64_t), 256);
     pack_tables(P);
@@ -513,7 +579,7 @@ mrg_status mrg_batch_plan_create(mrg_generator gen, const mrg_request* reqs, siz
     P->gen = gen;
     P->user.resize(n_req);
     for (size_t i = 0; i < n_req; ++i) P->user[i] = PlanReq{reqs[i], 0, 0};
-    P->tile_units = (cfg && cfg->tile_units) ? cfg->tile_units : kDefaultTileUnits;
+    P->tile_units = (cfg && cfg->tile_units) ? cfg->tile_units : automatic_tile_units(P->user);
     P->waves_per_simd = (cfg && cfg->waves_per_simd) ? cfg->waves_per_simd : kDefaultWavesPerSimd;
     P->wide = cfg ? cfg->wide_stores : 0;
     P->gang = (cfg && cfg->gang_waves) ? cfg->gang_waves : kDefaultGang;
@@ -563,7 +629,7 @@ mrg_status mrg_batch_autotune_workspace_size(const mrg_batch_plan* plan, size_t*
 
 mrg_status mrg_batch_tile_count(const mrg_batch_plan* plan, size_t* tiles) {
     if (!plan || !tiles) return mrg355_fail(MRG_E_INVALID_ARG, "NULL plan or tiles");
-    *tiles = plan->tiles.size();
+    *tiles = plan->cut;
     return MRG_OK;
 }
 

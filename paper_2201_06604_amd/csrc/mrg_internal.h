@@ -50,9 +50,14 @@ struct BatchReq {       // one request, static for a plan
 };
 
 struct BatchTile {      // a wave's unit of work
-    uint32_t req, sblk, chunk, pad;
+    uint32_t req;
+    uint32_t at;        // stream block; from bit kTileGapBit on, waves of its row group (narrow gangs): each
+                        // lane's second stream is 64 times that past its first, 0 = it has none
+    uint32_t chunk;
+    uint32_t gang_lo;   // of the gang with this tile's index: its first tile
 };
-constexpr uint32_t kNoRequest = 0xffffffffu;  // BatchTile.req of the padding of a short gang
+constexpr int kTileGapBit = 28;  // stream blocks: n_streams <= 2^31, 64 each
+constexpr uint32_t kTileBlockMask = (1u << kTileGapBit) - 1;
 
 struct BatchSlot {      // per-request counters, reset by every launch
     uint32_t remaining; // tiles not finished
@@ -89,7 +94,7 @@ struct BatchLaunch {    // kernel arguments
     uint32_t block_lo[kClasses + 1];  // and blocks [block_lo[c], block_lo[c+1])
     uint32_t wpb;                     // waves per block of the persistent kernel
     uint64_t fin_total;
-    uint32_t n_gangs;                 // gang mode: tiles[g*wpb .. g*wpb+wpb-1] is gang g; 0 = class queues
+    uint32_t n_gangs;                 // gang mode: gang g is tiles[g].gang_lo up to the next gang's; 0 = class queues
     uint32_t grid;                    // blocks of the persistent kernel
     uint32_t narrow;                  // gang mode: 1 = every tile is of one stream per lane
     uint32_t xq_lo[kXcdQueues + 1];   // gang mode: XCD x's queue holds gangs [xq_lo[x], xq_lo[x+1])

@@ -233,26 +233,35 @@ __device__ __forceinline__ void main_rows(const GenLaunch& L, uint32_t by, uint6
 // LOCK: workgroup barriers per unrolled main-loop iteration (three rows, or
 // three pairs for normals): 0, 1 (after the iteration) or 3 (after every row
 // or pair).
-template <int DIST, int DTYPE, int ARITH, int SPL, bool NT, int LOCK = 0>
-__device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uint32_t by) {
+// SPLIT: lane l owns streams s0 = 64 sblk + l and s0 + gap (SPL = 2, gap a
+// multiple of 64, s0 < S for every lane) and stores their values by themselves,
+// each wave instruction one run of 64: two chains a lane for any stream count
+// and alignment.  A second stream past the last is drawn from the last one's
+// state and its stores fall outside the row.
+template <int DIST, int DTYPE, int ARITH, int SPL, bool NT, int LOCK = 0, bool SPLIT = false>
+__device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uint32_t by, uint32_t gap = 0) {
     static_assert(LOCK == 0 || LOCK == 1 || LOCK == 3, "barriers per iteration");
+    static_assert(!SPLIT || SPL == 2, "two runs of streams");
     constexpr int G = ARITH == kArith31 ? kGen31k3p : kGen32k3a;
     using Engine = typename std::conditional<ARITH == kArithInt, IntEngine, F64EngineOf<G>>::type;
     using T = typename ElemOf<DTYPE>::T;
     constexpr uint32_t ESZ = sizeof(T);
-    constexpr uint32_t WS = 64 * SPL;                   // streams per wave
+    constexpr uint32_t WS = SPLIT ? 64 : 64 * SPL;      // streams per wave (of a run)
+    constexpr uint32_t LS = SPLIT ? 1 : SPL;            // a lane's neighbouring streams
     constexpr uint64_t kSpu = DIST == kNormal ? 2 : 1;  // steps per unit
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t S = L.S;
     const uint32_t first = sblk * WS;
-    const uint32_t s0 = first + lane * SPL;
-    if (s0 >= S) return;  // S % SPL == 0: a lane's streams are all present or all absent
+    const uint32_t s0 = first + lane * LS;
+    if (s0 >= S) return;  // S % SPL == 0: a lane's neighbouring streams are all present or all absent
+    const auto stream = [&](int i) { return SPLIT ? s0 + i * gap : s0 + i; };
+    const auto present = [&](int i) { return !SPLIT || i == 0 || s0 + gap < S; };
 
     // Work is counted in units: draws, or Box-Muller pairs for normals.
     uint64_t cnt[SPL], units[SPL];
 #pragma unroll
     for (int i = 0; i < SPL; ++i) {
-        cnt[i] = L.q + (s0 + i < L.r ? 1 : 0);
+        cnt[i] = present(i) ? L.q + (stream(i) < L.r ? 1 : 0) : 0;
         units[i] = DIST == kNormal ? (cnt[i] + 1) / 2 : cnt[i];
     }
     uint64_t u0, u1, kend;
@@ -265,7 +274,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
     Engine e[SPL];
 #pragma unroll
     for (int i = 0; i < SPL; ++i) {
-        const uint32_t* rec = L.streams + static_cast<uint64_t>(s0 + i) * 18;
+        const uint32_t* rec = L.streams + static_cast<uint64_t>(present(i) ? stream(i) : S - 1) * 18;
         uint32_t x[6];
 #pragma unroll
         for (int w = 0; w < 6; ++w) x[w] = rec[w];
@@ -281,9 +290,23 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
     const uint64_t rowstep = static_cast<uint64_t>(S) * ESZ;
     const uint64_t rest = static_cast<uint64_t>(S - first) * ESZ;
     const uint32_t nrec = rest > 0xffffffffull ? 0xffffffffu : static_cast<uint32_t>(rest);
-    const uint32_t voff = lane * SPL * ESZ;
+    const uint32_t voff = lane * LS * ESZ;
     const char* row = static_cast<const char*>(L.out) + (u0 * kSpu * S + first) * ESZ;
     uint64_t k = u0;
+    // a lane's values of one row
+    const auto store_row = [&](const char* at, const Pack<T, SPL>& p) {
+        if constexpr (SPLIT) {
+            store_1<T, NT>(row_rsrc(at, nrec), voff, p.v[0]);
+            store_1<T, NT>(row_rsrc(at + gap * ESZ, nrec - gap * ESZ), voff, p.v[1]);
+        } else {
+            store_n<T, SPL, NT>(row_rsrc(at, nrec), voff, p);
+        }
+    };
+    // one value of a ragged row
+    const auto store_value = [&](const char* at, int i, T v) {
+        if constexpr (SPLIT) store_1<T, NT>(row_rsrc(at + i * gap * ESZ, nrec - i * gap * ESZ), voff, v);
+        else store_1<T, NT>(row_rsrc(at, nrec), voff + i * ESZ, v);
+    };
 
     if constexpr (DIST == kNormal) {
         // 3 pairs = 6 steps per iteration: the register ring returns home.
@@ -298,11 +321,9 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
                 px.v[i] = narrow<DTYPE>(x);
                 py.v[i] = narrow<DTYPE>(y);
             }
-            store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, px);
-            row += rowstep;
-            store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, py);
-            row += rowstep;
-            if constexpr (LOCK == 3) __builtin_amdgcn_s_barrier();
+            store_row(row, px);
+            store_row(row + rowstep, py);
+            row += 2 * rowstep;
         };
         for (; k + 3 <= kend; k += 3) {
             pair([&kr](Engine& g, double& x, double& y) {
@@ -310,33 +331,27 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
                 auto z1 = g.template step<1>(kr);
                 box_muller<G, DTYPE>(z0, z1, x, y);
             });
+            if constexpr (LOCK == 3) __builtin_amdgcn_s_barrier();
             pair([&kr](Engine& g, double& x, double& y) {
                 auto z2 = g.template step<2>(kr);
                 auto z3 = g.template step<0>(kr);
                 box_muller<G, DTYPE>(z2, z3, x, y);
             });
+            if constexpr (LOCK == 3) __builtin_amdgcn_s_barrier();
             pair([&kr](Engine& g, double& x, double& y) {
                 auto z4 = g.template step<1>(kr);
                 auto z5 = g.template step<2>(kr);
                 box_muller<G, DTYPE>(z4, z5, x, y);
             });
+            if constexpr (LOCK == 3) __builtin_amdgcn_s_barrier();
             if constexpr (LOCK == 1) __builtin_amdgcn_s_barrier();
         }
         for (; k < kend; ++k) {
-            Pack<T, SPL> px, py;
-#pragma unroll
-            for (int i = 0; i < SPL; ++i) {
-                auto z0 = e[i].step_rot(kr);
-                auto z1 = e[i].step_rot(kr);
-                double x, y;
+            pair([&kr](Engine& g, double& x, double& y) {
+                auto z0 = g.step_rot(kr);
+                auto z1 = g.step_rot(kr);
                 box_muller<G, DTYPE>(z0, z1, x, y);
-                px.v[i] = narrow<DTYPE>(x);
-                py.v[i] = narrow<DTYPE>(y);
-            }
-            store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, px);
-            row += rowstep;
-            store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, py);
-            row += rowstep;
+            });
         }
         // Ragged tail (at most one pair): X and Y only where they exist.
         const uint64_t tend = min(u1, units[0]);
@@ -348,9 +363,8 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
                     auto z1 = e[i].step_rot(kr);
                     double x, y;
                     box_muller<G, DTYPE>(z0, z1, x, y);
-                    if (2 * k < cnt[i]) store_1<T, NT>(row_rsrc(row, nrec), voff + i * ESZ, narrow<DTYPE>(x));
-                    if (2 * k + 1 < cnt[i])
-                        store_1<T, NT>(row_rsrc(row + rowstep, nrec), voff + i * ESZ, narrow<DTYPE>(y));
+                    if (2 * k < cnt[i]) store_value(row, i, narrow<DTYPE>(x));
+                    if (2 * k + 1 < cnt[i]) store_value(row + rowstep, i, narrow<DTYPE>(y));
                 }
             }
             row += 2 * rowstep;
@@ -364,13 +378,13 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
                 p1.v[i] = value1<DIST, DTYPE, G>(e[i].template step<1>(kr), half_inv_rate);
                 p2.v[i] = value1<DIST, DTYPE, G>(e[i].template step<2>(kr), half_inv_rate);
             }
-            store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, p0);
+            store_row(row, p0);
             row += rowstep;
             if constexpr (LOCK == 3) __builtin_amdgcn_s_barrier();
-            store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, p1);
+            store_row(row, p1);
             row += rowstep;
             if constexpr (LOCK == 3) __builtin_amdgcn_s_barrier();
-            store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, p2);
+            store_row(row, p2);
             row += rowstep;
             if constexpr (LOCK != 0) __builtin_amdgcn_s_barrier();
         }
@@ -378,7 +392,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
             Pack<T, SPL> p;
 #pragma unroll
             for (int i = 0; i < SPL; ++i) p.v[i] = value1<DIST, DTYPE, G>(e[i].step_rot(kr), half_inv_rate);
-            store_n<T, SPL, NT>(row_rsrc(row, nrec), voff, p);
+            store_row(row, p);
             row += rowstep;
         }
         const uint64_t tend = min(u1, units[0]);
@@ -386,8 +400,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
 #pragma unroll
             for (int i = 0; i < SPL; ++i)
                 if (k < units[i])
-                    store_1<T, NT>(row_rsrc(row, nrec), voff + i * ESZ,
-                                   value1<DIST, DTYPE, G>(e[i].step_rot(kr), half_inv_rate));
+                    store_value(row, i, value1<DIST, DTYPE, G>(e[i].step_rot(kr), half_inv_rate));
             row += rowstep;
         }
     }
@@ -398,9 +411,10 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
     if (L.n_chunks == 1 && !L.no_writeback) {
 #pragma unroll
         for (int i = 0; i < SPL; ++i) {
+            if (!present(i)) continue;
             uint32_t x[6];
             e[i].save(x);
-            uint32_t* rec = L.streams + static_cast<uint64_t>(s0 + i) * 18;
+            uint32_t* rec = L.streams + static_cast<uint64_t>(stream(i)) * 18;
 #pragma unroll
             for (int w = 0; w < 6; ++w) rec[w] = x[w];
         }
@@ -573,7 +587,7 @@ __device__ __forceinline__ void batch_worker(const BatchLaunch& B, uint32_t firs
         if (q >= count) break;
         const uint32_t t = lo + q;
         const uint32_t req = __builtin_amdgcn_readfirstlane(B.tiles[t].req);
-        const uint32_t sblk = __builtin_amdgcn_readfirstlane(B.tiles[t].sblk);
+        const uint32_t sblk = __builtin_amdgcn_readfirstlane(B.tiles[t].at);
         const uint32_t chunk = __builtin_amdgcn_readfirstlane(B.tiles[t].chunk);
         const uint32_t kind = __builtin_amdgcn_readfirstlane(B.reqs[req].kind);
         const GenLaunch& L = B.reqs[req].L;
@@ -638,26 +652,36 @@ __global__ void __launch_bounds__(256) batch_kernel(BatchLaunch B) {
 }
 
 // ---------------------------------------------------------- gang batching
-// A gang is G wave tiles (G = waves per block) that one block runs together:
-// wave w takes tile w of the gang, and the waves pass a workgroup barrier after
-// every three rows (pairs, for normals) of their main loops.  The host puts consecutive
-// stream blocks of one request and chunk in a gang, so the row segments of
-// neighbouring waves -- which share a cache line wherever a row does not start
-// on a 128-byte line -- are written within a few rows of each other and the
-// line is completed in this CU's L2 instead of reaching HBM in two partial
-// writes.  Every wave passes as many barriers as the gang's longest main loop
-// (each wave works out every tile's count with the rule run_chunk follows).
+// A gang is up to G wave tiles (G = waves per block) that one block runs
+// together: wave w takes tile w of the gang, and the waves pass a workgroup
+// barrier after every three rows (pairs, for normals) of their main loops.  The
+// host puts all stream blocks of one request and chunk in a gang (a wave of a
+// narrow plan takes two where they outnumber the waves), so that rows are
+// written whole, within a few rows of each other, and the lines that row
+// segments share are completed in this CU's L2 instead of reaching HBM in two
+// partial writes.  Every wave passes as many barriers as the gang's longest main
+// loop (each wave works out every tile's count with the rule run_chunk follows).
 // Gangs of every class share one queue, which the host interleaves so that the
 // classes advance at the same pace: transform-heavy and store-heavy tiles run
 // side by side throughout the launch and finish together.
-// One barrier per unrolled iteration (three rows) rather than per row: the
-// 4,096-request mix ran 7.49 ms against 7.53 ms (gangs of 8, one stream per
-// lane); with none at all, waves drift apart and the shared lines are no
-// longer completed in L2.
+//
+// The 4,096-request mix (25.7 GB): 7.29 ms with gangs filled to the last wave
+// and rows cut wherever that fell, 6.24 with whole rows, 6.17 with 384-unit
+// tiles.  Its stores alone take 5.4 ms, its arithmetic alone 5.4 (the sustained
+// clock is 1.7 to 1.9 GHz); six waves a SIMD (80 registers) 6.45, gangs of 4
+// 7.04.  One barrier per three rows against one per row: 6.24 and 6.29 ms; with
+// none at all waves drift apart and the shared lines are no longer completed in
+// L2 (8.9 ms).
 #ifndef MRG_GANG_LOCK
 #define MRG_GANG_LOCK 1
 #endif
 constexpr int kGangLock = MRG_GANG_LOCK;  // barriers per unrolled main-loop iteration (0, 1 or 3)
+
+template <int DIST, int DTYPE>
+__device__ __forceinline__ void split_tile(const GenLaunch& L, uint32_t sblk, uint32_t chunk, uint32_t gap) {
+    if (gap) run_chunk<DIST, DTYPE, kArithF64, 2, false, kGangLock, true>(L, sblk, chunk, gap);
+    else run_chunk<DIST, DTYPE, kArithF64, 1, false, kGangLock>(L, sblk, chunk);
+}
 
 template <int KIND>
 __device__ __forceinline__ void gang_tile(const GenLaunch& L, uint32_t sblk, uint32_t chunk) {
@@ -679,11 +703,9 @@ __device__ __forceinline__ void gang_tile(const GenLaunch& L, uint32_t sblk, uin
 
 // Main-loop iterations of a wave tile: run_chunk passes kGangLock barriers
 // per iteration, and its main loop runs floor((kend - u0) / 3) of them, with u0
-// and kend as main_rows gives them (0 for the padding of a short gang).  Every
-// operand is wave-uniform.
+// and kend as main_rows gives them.  Every operand is wave-uniform.
 __device__ __forceinline__ uint32_t tile_iters(const BatchLaunch& B, const BatchTile& T) {
     const uint32_t req = __builtin_amdgcn_readfirstlane(T.req);
-    if (req == kNoRequest) return 0;
     const GenLaunch& L = B.reqs[req].L;
     const uint32_t chunk = __builtin_amdgcn_readfirstlane(T.chunk);
     uint64_t u0, u1, kend;
@@ -702,9 +724,9 @@ __device__ __forceinline__ uint32_t tile_iters(const BatchLaunch& B, const Batch
 // wave can overwrite it before every wave has read it.  All control flow
 // around the barriers is block-uniform.
 //
-// NARROW: the plan holds only tiles of one stream per lane.  Their code alone
-// fits the registers of six resident waves per SIMD, where the code of every
-// kind together allows three.
+// NARROW: the plan holds only requests of one stream per lane, or two of them
+// a gap apart.  Their code alone fits the registers of five resident waves per
+// SIMD, where the code of every kind together allows three.
 template <bool NARROW>
 __device__ __forceinline__ void gang_loop(const BatchLaunch& B) {
     stage_tables<kStageNormal>();
@@ -734,28 +756,33 @@ __device__ __forceinline__ void gang_loop(const BatchLaunch& B) {
             __syncthreads();
         }
         if (g == kNone) break;
-        const BatchTile* gt = B.tiles + static_cast<uint64_t>(g) * B.wpb;
+        const uint32_t lo = __builtin_amdgcn_readfirstlane(B.tiles[g].gang_lo);
+        const uint32_t end = g + 1 < B.n_gangs ? __builtin_amdgcn_readfirstlane(B.tiles[g + 1].gang_lo) : B.n_tiles;
+        const uint32_t members = end - lo;
+        const BatchTile* gt = B.tiles + lo;
         uint32_t nbar = 0, nit = 0;
-        for (uint32_t w = 0; w < B.wpb; ++w) {
+        for (uint32_t w = 0; w < members; ++w) {
             const uint32_t it = tile_iters(B, gt[w]);
             nbar = it > nbar ? it : nbar;
             if (w == wave) nit = it;
         }
-        const uint32_t req = __builtin_amdgcn_readfirstlane(gt[wave].req);
-        if (req != kNoRequest) {
-            const uint32_t sblk = __builtin_amdgcn_readfirstlane(gt[wave].sblk);
+        if (wave < members) {
+            const uint32_t req = __builtin_amdgcn_readfirstlane(gt[wave].req);
+            const uint32_t at = __builtin_amdgcn_readfirstlane(gt[wave].at);
+            const uint32_t sblk = at & kTileBlockMask;
             const uint32_t chunk = __builtin_amdgcn_readfirstlane(gt[wave].chunk);
             const uint32_t kind = __builtin_amdgcn_readfirstlane(B.reqs[req].kind);
             const GenLaunch& L = B.reqs[req].L;
             if constexpr (NARROW) {
+                const uint32_t gap = 64 * (at >> kTileGapBit);
                 switch (kind) {
-                    case kBUniF64x1: gang_tile<kBUniF64x1>(L, sblk, chunk); break;
-                    case kBUniF32x1: gang_tile<kBUniF32x1>(L, sblk, chunk); break;
-                    case kBRawU32x1: gang_tile<kBRawU32x1>(L, sblk, chunk); break;
-                    case kBNormF64: gang_tile<kBNormF64>(L, sblk, chunk); break;
-                    case kBNormF32: gang_tile<kBNormF32>(L, sblk, chunk); break;
-                    case kBExpF64: gang_tile<kBExpF64>(L, sblk, chunk); break;
-                    default: gang_tile<kBExpF32>(L, sblk, chunk); break;
+                    case kBUniF64x1: split_tile<kUniform, kF64>(L, sblk, chunk, gap); break;
+                    case kBUniF32x1: split_tile<kUniform, kF32>(L, sblk, chunk, gap); break;
+                    case kBRawU32x1: split_tile<kRaw, kU32>(L, sblk, chunk, gap); break;
+                    case kBNormF64: split_tile<kNormal, kF64>(L, sblk, chunk, gap); break;
+                    case kBNormF32: split_tile<kNormal, kF32>(L, sblk, chunk, gap); break;
+                    case kBExpF64: split_tile<kExponential, kF64>(L, sblk, chunk, gap); break;
+                    default: split_tile<kExponential, kF32>(L, sblk, chunk, gap); break;
                 }
             } else {
                 switch (kind) {
@@ -794,7 +821,7 @@ __device__ __forceinline__ void gang_loop(const BatchLaunch& B) {
 
 __global__ void __launch_bounds__(512) batch_gang_kernel(BatchLaunch B) { gang_loop<false>(B); }
 
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6)))
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5)))
 batch_gang_narrow_kernel(BatchLaunch B) {
     gang_loop<true>(B);
 }
