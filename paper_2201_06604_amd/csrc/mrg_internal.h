@@ -30,6 +30,7 @@ struct GenLaunch {
     uint64_t offset;     // steps every stream is advanced before its first draw
     int no_writeback;    // 1 = leave the stream records untouched (served requests)
     int lock;            // 1 = the waves of a block write each row together (barrier per row)
+    int column;          // 1 = a block's waves take the chunks of one stream block (set by plan_generate)
 };
 
 // Resolve chunk/n_chunks/block/arith left at 0 to the automatic choice.

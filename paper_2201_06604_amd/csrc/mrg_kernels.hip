@@ -238,7 +238,10 @@ __device__ __forceinline__ void main_rows(const GenLaunch& L, uint32_t by, uint6
 // each wave instruction one run of 64: two chains a lane for any stream count
 // and alignment.  A second stream past the last is drawn from the last one's
 // state and its stores fall outside the row.
-template <int DIST, int DTYPE, int ARITH, int SPL, bool NT, int LOCK = 0, bool SPLIT = false>
+// COLUMN: the block's waves hold all chunks of this stream block, so each
+// stream's last chunk writes its state back; the barrier keeps that behind every
+// wave's read of it.
+template <int DIST, int DTYPE, int ARITH, int SPL, bool NT, int LOCK = 0, bool SPLIT = false, bool COLUMN = false>
 __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uint32_t by, uint32_t gap = 0) {
     static_assert(LOCK == 0 || LOCK == 1 || LOCK == 3, "barriers per iteration");
     static_assert(!SPLIT || SPL == 2, "two runs of streams");
@@ -272,18 +275,28 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
 
     const typename Engine::Regs kr;
     Engine e[SPL];
+    uint32_t x[SPL][6];
 #pragma unroll
     for (int i = 0; i < SPL; ++i) {
         const uint32_t* rec = L.streams + static_cast<uint64_t>(present(i) ? stream(i) : S - 1) * 18;
-        uint32_t x[6];
 #pragma unroll
-        for (int w = 0; w < 6; ++w) x[w] = rec[w];
-        const uint64_t jump = L.offset + u0 * kSpu;
+        for (int w = 0; w < 6; ++w) x[i][w] = rec[w];
+    }
+    if constexpr (COLUMN) {
+#pragma unroll
+        for (int i = 0; i < SPL; ++i)  // the words are here, not on their way
+#pragma unroll
+            for (int w = 0; w < 6; ++w) asm volatile("" : "+v"(x[i][w]));
+        __builtin_amdgcn_s_barrier();
+    }
+    const uint64_t jump = L.offset + u0 * kSpu;
+#pragma unroll
+    for (int i = 0; i < SPL; ++i) {
         if (jump) {
-            if constexpr (ARITH == kArithInt) dev_jump<G>(x, jump);
-            else dev_jump_digits<G>(x, jump);
+            if constexpr (ARITH == kArithInt) dev_jump<G>(x[i], jump);
+            else dev_jump_digits<G>(x[i], jump);
         }
-        e[i].load(x);
+        e[i].load(x[i]);
     }
 
     const double half_inv_rate = L.param;
@@ -405,18 +418,17 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
         }
     }
 
-    // A stream owned by a single work-item is written back here; otherwise
-    // finalize_kernel advances it after this launch (other chunks of the same
-    // stream may not have read it yet).
-    if (L.n_chunks == 1 && !L.no_writeback) {
+    // A stream owned by a single work-item, or by the waves of this block, is
+    // written back here; otherwise finalize_kernel advances it after this
+    // launch (other chunks of the same stream may not have read it yet).
+    if ((COLUMN || L.n_chunks == 1) && !L.no_writeback) {
 #pragma unroll
         for (int i = 0; i < SPL; ++i) {
-            if (!present(i)) continue;
-            uint32_t x[6];
-            e[i].save(x);
+            if (!present(i) || (COLUMN && (u1 < units[i] || u0 >= units[i]))) continue;  // another chunk is its last
+            e[i].save(x[i]);
             uint32_t* rec = L.streams + static_cast<uint64_t>(stream(i)) * 18;
 #pragma unroll
-            for (int w = 0; w < 6; ++w) rec[w] = x[w];
+            for (int w = 0; w < 6; ++w) rec[w] = x[i][w];
         }
     }
 }
@@ -458,20 +470,43 @@ __global__ void __launch_bounds__(1024) gen_kernel(GenLaunch L) {
     run_chunk<DIST, DTYPE, ARITH, SPL, NT, LOCK ? 3 : 0>(L, sblk, by);
 }
 
+// Launches of no more chunks than a block has waves: block bx holds stream block
+// bx, wave w its chunk w, and no kernel has to advance the states afterwards.
+// These calls are bound by latency: a second launch, and the jumps in it, cost
+// about as much as the draws.  64 streams x 156 fp32 uniforms 6.6 -> 4.7 us, fp32
+// exponentials 8.1 -> 6.0; 2,048 x 64 fp64 normals 9.6 -> 4.9.
+template <int DIST, int DTYPE, int ARITH, int SPL, bool NT>
+__global__ void __launch_bounds__(1024) gen_column_kernel(GenLaunch L) {
+    stage_for<DIST, DTYPE>();
+    uint32_t bx = blockIdx.x;
+    if (L.xcd) bx = (bx % 8) * (gridDim.x / 8) + bx / 8;  // host guarantees gridDim.x % 8 == 0
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    run_chunk<DIST, DTYPE, ARITH, SPL, NT, 0, false, true>(L, bx, wave);
+}
+
 // cur <- A^(steps consumed) cur for every stream, after a chunked launch:
-// cnt_s = q + (s < r) draws; normals consume 2*ceil(cnt_s/2) steps.
+// cnt_s = q + (s < r) draws; normals consume 2*ceil(cnt_s/2) steps.  All streams
+// jump by the shorter count -- one exponent for the whole launch, so the tables
+// are scalar loads -- and the first r step on from there.
 template <int G>
 __global__ void __launch_bounds__(256) finalize_kernel(uint32_t* streams, uint32_t S, uint64_t q,
                                                        uint32_t r, int normal) {
     uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= S) return;
-    uint64_t cnt = q + (s < r ? 1 : 0);
-    uint64_t steps = normal ? (cnt + 1) / 2 * 2 : cnt;
+    const uint64_t steps = normal ? (q + 1) / 2 * 2 : q;
+    const uint32_t more = normal ? (q % 2 ? 0 : 2) : 1;
     uint32_t* rec = streams + static_cast<uint64_t>(s) * 18;
     uint32_t x[6];
 #pragma unroll
     for (int w = 0; w < 6; ++w) x[w] = rec[w];
-    dev_jump_digits<G>(x, steps);  // lanes hold one or two distinct counts
+    dev_jump_digits<G>(x, steps);
+    if (s < r && more) {
+        const F64Regs<G> kr;
+        F64EngineOf<G> e;
+        e.load(x);
+        for (uint32_t k = 0; k < more; ++k) e.step_rot(kr);
+        e.save(x);
+    }
 #pragma unroll
     for (int w = 0; w < 6; ++w) rec[w] = x[w];
 }
@@ -1028,23 +1063,8 @@ hipError_t launch_advance(int gen, uint32_t* streams, uint64_t n, uint64_t steps
     return hipGetLastError();
 }
 
-// Automatic launch shape, from measurements on MI355X at 2^30 draws over
-// 262,144 streams (interleaved medians):
-//   f64 uniforms   2 streams/lane (16-byte stores), ~2 waves per SIMD, each
-//                  stream whole in one work-item, 512 threads whose waves
-//                  pass a barrier per row (1.31 ms against 1.52 ms for the
-//                  same grid running free), XCD remap
-//   f32/u32        4 streams/lane, ~4 waves per SIMD, 512 threads, no remap
-//                  (VALU-bound: the per-row barrier costs ~5%)
-//   exponential    2 streams/lane, ~4 waves per SIMD (2 chunks per stream),
-//                  256 threads, XCD remap
-//   normal         2 streams/lane, ~8 waves per SIMD (flat from 2 to 16),
-//                  256 threads, XCD remap
-// Chunks hold at least 96 units (32 with one stream per lane on grids below
-// two waves per SIMD); at most 65535 chunks.  A narrower store is used when n_streams or the output
-// alignment does not allow the wide one.
-// Index of the tuned shape for a call: kind (dist, dtype) and size class of
-// its draw count.
+// The tuned shape of a call: kind (dist, dtype), size class and half of its
+// draw count, and whether its rows start on 128-byte lines.
 static const TunedShape& tuned_shape(const GenLaunch& L) {
     int kind;
     switch (L.dist) {
@@ -1055,7 +1075,8 @@ static const TunedShape& tuned_shape(const GenLaunch& L) {
     }
     const uint64_t n = L.q * L.S + L.r;
     const int cls = n < (1ull << 18) ? 0 : n < (1ull << 22) ? 1 : n < (1ull << 26) ? 2 : n < (1ull << 29) ? 3 : 4;
-    return kTuned[kind][cls];
+    const int esz = L.dtype == kF64 ? 8 : 4;
+    return kTuned[kind][cls][n >= kTunedHalf[cls] ? 1 : 0][static_cast<uint64_t>(L.S) * esz % 128 ? 1 : 0];
 }
 
 void plan_generate(GenLaunch& L) {
@@ -1098,13 +1119,23 @@ void plan_generate(GenLaunch& L) {
         nch = (units_max + c - 1) / c;
     }
     L.n_chunks = static_cast<uint32_t>(nch);
-    // Lockstep rows (store-bound fp64 uniforms): once the grid fills the
-    // chip (two waves per SIMD), the waves of a block writing each row
-    // together beat free-running waves; smaller grids are launch-latency-bound
+    // Lockstep rows: once the grid fills the chip (two waves per SIMD), the
+    // waves of a block writing each row together beat free-running waves where
+    // stores bound the call (65,536 x 4,096 fp64 uniforms: 457 -> 303 us) and
+    // where neighbouring waves share lines (262,143 x 4,096: fp64 normals 3.68 ->
+    // 1.76 ms, fp32 uniforms 2.16 -> 0.77 ms); smaller grids are latency-bound
     if (!cfg_given && t.lock) L.lock = n_sblk * nch >= 2048;
-    const uint64_t wpb = static_cast<uint64_t>(L.block) / 64;
-    const uint64_t gx = (n_sblk + wpb - 1) / wpb;
-    if (L.xcd && (gx * nch) % 8) L.xcd = 0;  // the remap needs a multiple of 8 blocks
+    uint64_t wpb = static_cast<uint64_t>(L.block) / 64;
+    L.column = !L.lock && nch > 1 && nch <= wpb;
+    // Neither rows in step nor a column keeps the waves of a block together:
+    // narrow blocks, so that a small grid spreads over more CUs (1,024 streams
+    // x 16 fp64 uniforms: 4.4 us in one block of 16 waves, 2.9 in four of 4)
+    if (!cfg_given && !L.lock && !L.column && n_sblk * nch < 2048 && L.block > 256) {
+        L.block = 256;
+        wpb = 4;
+    }
+    const uint64_t blocks = L.column ? n_sblk : (n_sblk + wpb - 1) / wpb * nch;
+    if (L.xcd && blocks % 8) L.xcd = 0;  // the remap needs a multiple of 8 blocks
 }
 
 template <int DIST, int DTYPE, int ARITH, int SPL, bool NT, bool LOCK>
@@ -1112,6 +1143,13 @@ static hipError_t launch_t(const GenLaunch& L, hipStream_t s) {
     const unsigned wpb = static_cast<unsigned>(L.block) / 64;
     const uint64_t ws = 64ull * SPL;
     const uint64_t n_sblk = (static_cast<uint64_t>(L.S) + ws - 1) / ws;
+    if constexpr (!LOCK) {
+        if (L.column) {
+            hipLaunchKernelGGL((gen_column_kernel<DIST, DTYPE, ARITH, SPL, NT>), dim3(static_cast<unsigned>(n_sblk)),
+                               dim3(64 * L.n_chunks), 0, s, L);
+            return hipGetLastError();
+        }
+    }
     dim3 grid(static_cast<unsigned>((n_sblk + wpb - 1) / wpb), L.n_chunks);
     hipLaunchKernelGGL((gen_kernel<DIST, DTYPE, ARITH, SPL, NT, LOCK>), grid, dim3(L.block), 0, s, L);
     return hipGetLastError();
@@ -1177,7 +1215,11 @@ __global__ void __launch_bounds__(1024) store_ceiling_kernel(GenLaunch L, T valu
     constexpr uint32_t ESZ = sizeof(T);
     constexpr uint32_t WS = 64 * SPL;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t sblk = bx * (blockDim.x >> 6) + wave;
+    if (L.column) {  // gen_column_kernel's map
+        by = wave;
+        if (by >= L.n_chunks) return;
+    }
+    const uint32_t sblk = L.column ? bx : bx * (blockDim.x >> 6) + wave;
     const bool live = sblk < (L.S + WS - 1) / WS;
     if (!LOCK && !live) return;
     const uint32_t lane = threadIdx.x & 63;
@@ -1205,6 +1247,7 @@ static hipError_t launch_ceiling_t(const GenLaunch& L, T value, hipStream_t s) {
     const unsigned wpb = static_cast<unsigned>(L.block) / 64;
     const uint64_t n_sblk = (static_cast<uint64_t>(L.S) + 64 * SPL - 1) / (64 * SPL);
     dim3 grid(static_cast<unsigned>((n_sblk + wpb - 1) / wpb), L.n_chunks);
+    if (L.column) grid = dim3(static_cast<unsigned>(n_sblk));
     if (L.nontemporal) {
         if (L.lock) hipLaunchKernelGGL((store_ceiling_kernel<T, SPL, true, true>), grid, dim3(L.block), 0, s, L, value);
         else hipLaunchKernelGGL((store_ceiling_kernel<T, SPL, true, false>), grid, dim3(L.block), 0, s, L, value);
@@ -1300,7 +1343,7 @@ hipError_t launch_batch(const BatchLaunch& B_in, unsigned grid, unsigned block, 
 hipError_t launch_generate(const GenLaunch& L, hipStream_t s) {
     if (L.n_chunks == 0) return hipSuccess;
     hipError_t e = launch_gen_only(L, s);
-    if (e != hipSuccess || L.n_chunks == 1 || L.no_writeback) return e;
+    if (e != hipSuccess || L.n_chunks == 1 || L.column || L.no_writeback) return e;
     if (L.arith == kArith31)
         hipLaunchKernelGGL(finalize_kernel<kGen31k3p>, dim3(grid1d(L.S, 256)), dim3(256), 0, s, L.streams, L.S,
                            L.q, L.r, L.dist == kNormal ? 1 : 0);
