@@ -177,11 +177,21 @@ def _check(st):
     return st
 
 
+_current = None  # torch's current device and raw stream of a device, once torch is imported
+
+
 def _stream(stream):
+    """The stream's address; without one, the current stream's.  Asked for as a
+    number: the object torch.cuda.current_stream() builds took 2.7 us of a small
+    call's 13, its address alone 0.3."""
+    global _current
     if stream is not None:
-        return ctypes.c_void_p(int(stream))
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return int(stream)
+    if _current is None:
+        import torch
+        _current = torch.cuda.current_device, torch._C._cuda_getCurrentRawStream
+    device, raw_stream = _current
+    return raw_stream(device())
 
 
 def _dptr(t):
@@ -189,10 +199,10 @@ def _dptr(t):
     if t is None:
         return None
     if isinstance(t, int):
-        return ctypes.c_void_p(t)
+        return t
     if not t.is_cuda:
         raise ValueError("expected a device (CUDA) tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _need(t, n_bytes, what, esz=None):
@@ -290,10 +300,11 @@ def mrg_generate(streams, n, dist=MRG_UNIFORM, dtype=MRG_F64, param=1.0, out=Non
     int32 tensor holding the raw 32-bit words.  `cfg` = dict with keys of
     CFG_KEYS selects a launch shape (results do not change)."""
     S = streams.shape[0] if n_streams is None else n_streams
+    _need(streams, S * REC_WORDS * 4, "stream records")
     if out is None:
         out = new_output(n, dtype)
-    _need(streams, S * REC_WORDS * 4, "stream records")
-    _need(out, n * (8 if dtype == MRG_F64 else 4), "output", 8 if dtype == MRG_F64 else 4)
+    else:
+        _need(out, n * (8 if dtype == MRG_F64 else 4), "output", 8 if dtype == MRG_F64 else 4)
     if cfg is None:
         st = lib().mrg_generate(gen, _dptr(streams), S, n, dist, dtype, param, _dptr(out),
                                 _stream(stream))
