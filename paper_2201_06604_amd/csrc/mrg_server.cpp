@@ -178,10 +178,12 @@ struct mrg_server {
     uint64_t in_flight = 0;
     std::thread th;
     std::atomic<bool> stop{false};
+    std::atomic<uint32_t> callers{0};  // API calls waiting for `mu`
     mrg_status error = MRG_OK;
 
     void loop();
-    bool launch_batch(Lane& L);
+    bool launch_batch(Lane& L, std::unique_lock<std::mutex>& lk);
+    hipError_t enqueue(Lane& L, const std::vector<PlanReq>& reqs, const char** what);
     bool launch_plain();
     bool poll_lanes();
     bool poll_plain();
@@ -198,6 +200,22 @@ struct mrg_server {
         }
     }
 };
+
+namespace {
+
+// `mu` for an API call.  The scheduler looks at its lanes in a tight loop, and a
+// thread that wakes up on the mutex finds it taken again: a call announces itself,
+// and the scheduler stays off the mutex until the callers have had it.
+struct CallerLock {
+    std::unique_lock<std::mutex> lk;
+    explicit CallerLock(mrg_server* s) : lk(s->mu, std::defer_lock) {
+        s->callers.fetch_add(1, std::memory_order_relaxed);
+        lk.lock();
+        s->callers.fetch_sub(1, std::memory_order_relaxed);
+    }
+};
+
+}  // namespace
 
 // ------------------------------------------------------------ scheduler
 void mrg_server::complete(uint64_t id, Ticket& t) {
@@ -274,8 +292,10 @@ bool mrg_server::poll_plain() {
 }
 
 // Admit pending requests in order while their outputs fit the pool, plan them
-// as one persistent launch and enqueue it on the lane.
-bool mrg_server::launch_batch(Lane& L) {
+// as one persistent launch and enqueue it on the lane.  The lane is the
+// scheduler's own, so the planning and the launch (11.6 us in the middle of a
+// burst) run without the mutex, and requests are taken meanwhile.
+bool mrg_server::launch_batch(Lane& L, std::unique_lock<std::mutex>& lk) {
     std::vector<uint64_t> ids;
     std::vector<PlanReq> reqs;
     while (!pending.empty() && ids.size() < cfg.max_batch) {
@@ -296,7 +316,30 @@ bool mrg_server::launch_batch(Lane& L) {
         pending.pop_front();
     }
     if (ids.empty()) return false;
-    if (ids.size() == 1) {  // nothing to batch with: one plain launch, no plan upload
+    lk.unlock();
+    const char* what = nullptr;
+    const hipError_t e = enqueue(L, reqs, &what);
+    lk.lock();
+    if (e != hipSuccess || what) {
+        if (e != hipSuccess) fail_hip(e, what);
+        else error = MRG_E_INVALID_ARG;  // refused by the planner
+        return false;
+    }
+    L.tickets = ids;
+    L.remaining = ids.size();
+    L.busy = true;
+    for (uint64_t id : ids) tickets.at(id).state = kInFlight;
+    in_flight += ids.size();
+    st.max_in_flight = std::max<uint64_t>(st.max_in_flight, in_flight);
+    ++st.launches;
+    note_lanes_busy();
+    return true;
+}
+
+// The lane's part of launch_batch: touches nothing that API calls share.
+// hipSuccess with *what set: the planner refused the requests.
+hipError_t mrg_server::enqueue(Lane& L, const std::vector<PlanReq>& reqs, const char** what) {
+    if (reqs.size() == 1) {  // nothing to batch with: one plain launch, no plan upload
         GenLaunch G{};
         G.streams = reinterpret_cast<uint32_t*>(reqs[0].q.streams);
         G.out = reqs[0].q.out;
@@ -311,26 +354,15 @@ bool mrg_server::launch_batch(Lane& L) {
         plan_generate(G);
         hipError_t e = launch_generate(G, L.stream);
         if (e == hipSuccess) e = hipEventRecord(L.done_ev, L.stream);
-        if (e != hipSuccess) {
-            fail_hip(e, "single launch");
-            return false;
-        }
-        L.single = true;
-        L.tickets = ids;
-        L.remaining = 1;
-        L.busy = true;
-        tickets.at(ids[0]).state = kInFlight;
-        in_flight += 1;
-        st.max_in_flight = std::max<uint64_t>(st.max_in_flight, in_flight);
-        ++st.launches;
-        note_lanes_busy();
-        return true;
+        if (e != hipSuccess) *what = "single launch";
+        else L.single = true;
+        return e;
     }
     mrg_batch_plan* plan = nullptr;
     for (uint32_t tu = cfg.tile_units;; tu *= 2) {  // coarser tiles until the plan fits the lane
         if (plan_internal(reqs, tu, &plan)) {
-            error = MRG_E_INVALID_ARG;
-            return false;
+            *what = "plan";
+            return hipSuccess;
         }
         if (plan_bytes(plan) <= L.ws_bytes || tu >= (1u << 30)) break;
         mrg_batch_plan_destroy(plan);
@@ -338,32 +370,21 @@ bool mrg_server::launch_batch(Lane& L) {
     }
     const size_t toff = plan_table_offset(plan);
     plan_pack_tables(plan, L.staging);
-    std::memset(L.slots_host, 0, ids.size() * sizeof(BatchSlot));
+    std::memset(L.slots_host, 0, reqs.size() * sizeof(BatchSlot));
+    L.plan = plan;  // the lane's from here on, also after an error
     hipError_t e = hipMemcpyAsync(static_cast<char*>(L.ws) + toff, L.staging, plan_bytes(plan) - toff,
                                   hipMemcpyHostToDevice, L.stream);
     if (e != hipSuccess) {
-        fail_hip(e, "table upload");
-        return false;
+        *what = "table upload";
+        return e;
     }
     if (plan_launch(plan, L.ws, L.slots_dev, L.stream)) {
-        error = MRG_E_HIP;
-        return false;
+        *what = "batch launch";
+        return hipErrorLaunchFailure;
     }
     e = hipEventRecord(L.done_ev, L.stream);
-    if (e != hipSuccess) {
-        fail_hip(e, "event record");
-        return false;
-    }
-    L.plan = plan;
-    L.tickets = ids;
-    L.remaining = ids.size();
-    L.busy = true;
-    for (uint64_t id : ids) tickets.at(id).state = kInFlight;
-    in_flight += ids.size();
-    st.max_in_flight = std::max<uint64_t>(st.max_in_flight, in_flight);
-    ++st.launches;
-    note_lanes_busy();
-    return true;
+    if (e != hipSuccess) *what = "event record";
+    return e;
 }
 
 // Baseline: the pending head, when its output fits, as one plain launch.
@@ -409,16 +430,25 @@ bool mrg_server::launch_plain() {
 // arrives within the window is picked up without a thread wake-up.
 constexpr uint64_t kSpinWindowNs = 2000000;
 
+// The longest the scheduler stays off the mutex for API calls that want it.
+constexpr uint64_t kGiveWayNs = 20000;
+
 void mrg_server::loop() {
     (void)hipSetDevice(device);
     std::unique_lock<std::mutex> lk(mu);
     uint64_t last_active = steady_ns();
     while (!stop.load()) {
+        if (callers.load(std::memory_order_relaxed)) {
+            lk.unlock();
+            const uint64_t until = steady_ns() + kGiveWayNs;
+            while (callers.load(std::memory_order_relaxed) && steady_ns() < until) std::this_thread::yield();
+            lk.lock();
+        }
         bool progress = cfg.mode == 0 ? poll_lanes() : poll_plain();
         if (error == MRG_OK) {
             if (cfg.mode == 0) {
                 for (Lane& L : lanes)
-                    if (!L.busy && !pending.empty() && launch_batch(L)) progress = true;
+                    if (!L.busy && !pending.empty() && launch_batch(L, lk)) progress = true;
             } else {
                 while (launch_plain()) progress = true;
             }
@@ -572,11 +602,11 @@ mrg_status mrg_server_submit(mrg_server* s, uint32_t session, uint64_t n, mrg_di
         return mrg355_fail(MRG_E_INVALID_ARG, "exponential rate must be finite and > 0");
     const size_t bytes = static_cast<size_t>(n) * esz_of(dtype);
     if (n > (SIZE_MAX / 8) || round256(bytes) > s->pool.total) {
-        std::lock_guard<std::mutex> g(s->mu);
+        CallerLock g(s);
         ++s->st.rejected;
         return mrg355_fail(MRG_E_NOMEM, "output of %zu bytes exceeds the pool", bytes);
     }
-    std::lock_guard<std::mutex> g(s->mu);
+    CallerLock g(s);
     if (s->error) return mrg355_fail(s->error, "server stopped after an error");
     const uint64_t per = (n + s->S - 1) / s->S;
     const uint64_t steps = dist == MRG_NORMAL ? (per + 1) / 2 * 2 : per;
@@ -603,7 +633,7 @@ mrg_status mrg_server_submit(mrg_server* s, uint32_t session, uint64_t n, mrg_di
 
 mrg_status mrg_server_poll(mrg_server* s, uint64_t ticket, int* done, void** dev_out, uint64_t* t_done_ns) {
     if (!s || !done) return mrg355_fail(MRG_E_INVALID_ARG, "NULL argument");
-    std::lock_guard<std::mutex> g(s->mu);
+    CallerLock g(s);
     auto it = s->tickets.find(ticket);
     if (it == s->tickets.end()) return mrg355_fail(MRG_E_INVALID_ARG, "unknown ticket");
     if (s->error) return mrg355_fail(s->error, "server stopped after an error");
@@ -616,7 +646,7 @@ mrg_status mrg_server_poll(mrg_server* s, uint64_t ticket, int* done, void** dev
 
 mrg_status mrg_server_release(mrg_server* s, uint64_t ticket) {
     if (!s) return mrg355_fail(MRG_E_INVALID_ARG, "NULL server");
-    std::lock_guard<std::mutex> g(s->mu);
+    CallerLock g(s);
     auto it = s->tickets.find(ticket);
     if (it == s->tickets.end()) return mrg355_fail(MRG_E_INVALID_ARG, "unknown ticket");
     if (it->second.state != kDone) return mrg355_fail(MRG_E_INVALID_ARG, "request not complete");
@@ -629,7 +659,7 @@ mrg_status mrg_server_release(mrg_server* s, uint64_t ticket) {
 
 mrg_status mrg_server_stats_get(mrg_server* s, mrg_server_stats* out) {
     if (!s || !out) return mrg355_fail(MRG_E_INVALID_ARG, "NULL argument");
-    std::lock_guard<std::mutex> g(s->mu);
+    CallerLock g(s);
     *out = s->st;
     out->pool_in_use = s->pool.in_use;
     out->pool_peak = s->pool.peak;
@@ -648,7 +678,7 @@ mrg_status mrg_server_drive(mrg_server* s, size_t n, const uint64_t* t_arrival_n
     }
     std::unordered_map<uint64_t, size_t> index;
     {
-        std::lock_guard<std::mutex> g(s->mu);
+        CallerLock g(s);
         s->collect = true;
         s->completions.clear();
     }
@@ -666,7 +696,8 @@ mrg_status mrg_server_drive(mrg_server* s, size_t n, const uint64_t* t_arrival_n
             index[id] = next++;
         }
         if (status) break;
-        std::unique_lock<std::mutex> lk(s->mu);
+        CallerLock g(s);
+        std::unique_lock<std::mutex>& lk = g.lk;
         if (s->error) {
             status = mrg355_fail(s->error, "server stopped after an error");
             break;
@@ -699,7 +730,7 @@ mrg_status mrg_server_drive(mrg_server* s, size_t n, const uint64_t* t_arrival_n
         }
     }
     {
-        std::lock_guard<std::mutex> g(s->mu);
+        CallerLock g(s);
         s->collect = false;
     }
     if (span_ns) *span_ns = last - t0;
