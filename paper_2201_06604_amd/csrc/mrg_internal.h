@@ -161,6 +161,7 @@ struct PaperLaunch {
     uint32_t n_cb;       // ... in n_cb column blocks
     int dist, dtype;
     double param;        // 1/(2 rate) for exponentials (times -2 log u)
+    int paired;          // normals: X and Y of every pair may leave in one aligned store
 };
 void plan_paper(PaperLaunch& L, int gen);
 hipError_t launch_paper(const PaperLaunch& L, int gen, hipStream_t s);

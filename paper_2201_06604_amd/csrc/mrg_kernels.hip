@@ -1431,22 +1431,52 @@ __global__ void __launch_bounds__(256) paper_kernel(PaperLaunch L) {
     }
     T* out = static_cast<T*>(L.out);
     const double half_inv_rate = L.param;
-    for (uint32_t i = i0; i < i1; ++i) {
-        T* row = out + (g0 + static_cast<uint64_t>(i) * L.G0) * L.npad;
-        for (uint32_t j = j0, c = g1 + j0 * L.G1; j < j1; ++j, c += L.G1) {
-            if constexpr (DIST == kNormal) {
-                auto z1 = ea.step_rot(kr);
-                auto z2 = eb.step_rot(kr);
-                double xv, yv;
-                box_muller<G, DTYPE>(z1, z2, xv, yv);
-                __builtin_nontemporal_store(narrow<DTYPE>(xv), row + c);
-                __builtin_nontemporal_store(narrow<DTYPE>(yv), row + c + 1);
+    // One visit: step P of three (the register ring returns home), -1: a step
+    // that rotates it.  PAIR: X and Y leave in one store.
+    const auto visit = [&](auto step, auto pair, T* at) {
+        constexpr int P = decltype(step)::value;
+        const auto next = [&kr](Engine& e) {
+            if constexpr (P < 0) return e.step_rot(kr);
+            else return e.template step<P>(kr);
+        };
+        if constexpr (DIST == kNormal) {
+            auto z1 = next(ea);
+            auto z2 = next(eb);
+            double xv, yv;
+            box_muller<G, DTYPE>(z1, z2, xv, yv);
+            if constexpr (decltype(pair)::value) {
+                typedef T T2 __attribute__((ext_vector_type(2)));
+                __builtin_nontemporal_store(T2{narrow<DTYPE>(xv), narrow<DTYPE>(yv)}, reinterpret_cast<T2*>(at));
             } else {
-                __builtin_nontemporal_store(value1<DIST, DTYPE, G>(ea.step_rot(kr), half_inv_rate), row + c);
+                __builtin_nontemporal_store(narrow<DTYPE>(xv), at);
+                __builtin_nontemporal_store(narrow<DTYPE>(yv), at + 1);
             }
+        } else {
+            __builtin_nontemporal_store(value1<DIST, DTYPE, G>(next(ea), half_inv_rate), at);
         }
-        if (L.n_cb > 1) break;  // a column block covers one row
-    }
+    };
+    // Three visits an iteration save the register rotation (fp64 normals of 10^4 x
+    // 10^4 on 512 x 128: 190 -> 174 us, fp32 exponentials 134 -> 105).  Where a
+    // visit is one 8-byte store a lane, stores bound the launch and waves that run
+    // visits in bursts reach memory in a worse order (fp64 uniforms 148 -> 165,
+    // exponentials 154 -> 171): those go one by one.
+    constexpr bool kThree = DTYPE != kF64 || DIST == kNormal;
+    const auto rows = [&](auto pair) {
+        for (uint32_t i = i0; i < i1; ++i) {
+            T* at = out + (g0 + static_cast<uint64_t>(i) * L.G0) * L.npad + g1 + static_cast<uint64_t>(j0) * L.G1;
+            uint32_t j = j0;
+            if constexpr (kThree) for (; j + 3 <= j1; j += 3) {
+                visit(std::integral_constant<int, 0>{}, pair, at);
+                visit(std::integral_constant<int, 1>{}, pair, at + L.G1);
+                visit(std::integral_constant<int, 2>{}, pair, at + 2 * static_cast<uint64_t>(L.G1));
+                at += 3 * static_cast<uint64_t>(L.G1);
+            }
+            for (; j < j1; ++j, at += L.G1) visit(std::integral_constant<int, -1>{}, pair, at);
+            if (L.n_cb > 1) break;  // a column block covers one row
+        }
+    };
+    if (DIST == kNormal && L.paired) rows(std::true_type{});
+    else rows(std::false_type{});
     if (L.n_rb == 1 && L.n_cb == 1) {
         ea.save(x);
 #pragma unroll
@@ -1507,25 +1537,20 @@ static int paper_blocks_per_cu_g(int dist, int dtype) {
     }
 }
 
-// Chunks per work-item: about as many as fill a whole number of rounds of
-// the waves the device holds at once -- one for normals and exponentials, so
-// that every lane runs one chunk of about equal length and no partly filled
-// round trails the launch, three for uniforms and raw words, whose stores
-// keep more waves busy over time -- in whole rows while a work-item has
-// enough of them, else in blocks of one row's visits.  The 10^4 x 10^4
-// normals of Section 3.1 on a 512 x 128 lattice (32,768 pairs, 20 rows of
-// 78-79 visits each): 0.29 ms against 0.41 ms in one-row blocks for 2^20
-// lanes with per-bit jumps; fp64 uniforms 0.165 against 0.18 ms.
-#ifndef MRG_PAPER_ROUNDS
-#define MRG_PAPER_ROUNDS 1
-#endif
-#ifndef MRG_PAPER_ROUNDS_PLAIN
-#define MRG_PAPER_ROUNDS_PLAIN 3
-#endif
-constexpr uint64_t kPaperRounds = MRG_PAPER_ROUNDS;             // normals, exponentials
-constexpr uint64_t kPaperRoundsPlain = MRG_PAPER_ROUNDS_PLAIN;  // uniforms, raw (store-bound)
+// Chunks per work-item: about as many as fill one round of the waves the device
+// holds at once, so that every lane runs one chunk of about equal length and no
+// partly filled round trails the launch, in whole rows while a work-item has
+// enough of them, else in blocks of one row's visits.  Uniforms and raw words take
+// up to three rounds while a chunk keeps kPaperVisits visits: their stores reach
+// memory in a better order (10^4 x 10^4 on 512 x 128: fp64 uniforms 165 us in one
+// round, 148 in three), but a chunk starts with a jump (3,000 x 4,000 on 256 x 64:
+// 21 us in one round, 34 in three of 8 visits each).
+constexpr uint64_t kPaperRoundsPlain = 3;
+constexpr uint64_t kPaperVisits = 32;
 
 void plan_paper(PaperLaunch& L, int gen) {
+    // g1 is even for pairs, so a pair's place is even in its row
+    L.paired = L.npad % 2 == 0 && reinterpret_cast<uintptr_t>(L.out) % (L.dtype == kF64 ? 16 : 8) == 0;
     L.lanes_g1 = L.dist == kNormal ? L.G1 / 2 : L.G1;
     const uint64_t nr_max = (static_cast<uint64_t>(L.nrow) + L.G0 - 1) / L.G0;
     const uint64_t nc_max = (static_cast<uint64_t>(L.ncol) + L.G1 - 1) / L.G1;
@@ -1533,7 +1558,9 @@ void plan_paper(PaperLaunch& L, int gen) {
     const int per_cu = gen == kGen31k3p ? paper_blocks_per_cu_g<kGen31k3p>(L.dist, L.dtype)
                                         : paper_blocks_per_cu_g<kGen32k3a>(L.dist, L.dtype);
     const uint64_t resident = static_cast<uint64_t>(device_cu_count()) * static_cast<uint64_t>(per_cu) * 256;
-    const uint64_t rounds = L.dist == kUniform || L.dist == kRaw ? kPaperRoundsPlain : kPaperRounds;
+    uint64_t rounds = 1;
+    if (L.dist == kUniform || L.dist == kRaw)
+        while (rounds < kPaperRoundsPlain && (rounds + 1) * resident * kPaperVisits <= items * nr_max * nc_max) ++rounds;
     const uint64_t want = std::max<uint64_t>(1, rounds * resident / std::max<uint64_t>(1, items));
     if (want <= nr_max || nc_max <= 1) {
         L.rows_per = static_cast<uint32_t>((nr_max + want - 1) / want);
