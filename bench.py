@@ -50,9 +50,10 @@ OPS_PER_DRAW = {"f64_uniform": 18.2, "f32_uniform": 19.6, "f64_normal": 54.9, "f
                 "f32_normal": 36.1, "f32_exponential": 32.2}
 # The same for the contingency-table kernels: lane-instructions per table of
 # the 10^6-table mix and per Fisher replicate of the 7 x 12 table, counted with
-# SQ_INSTS_VALU on the tables kernel with 6 checkpoints and the Fisher kernel
-# with 8 (their inversion loops' trip counts depend on the margins), frozen
-OPS_PER_TABLE = {"tables_kernel": 43136.9, "fisher_kernel": 692654.1}
+# SQ_INSTS_VALU.  They changed method as well (one bounded search per entry in
+# place of two passes with a division per value: 43,136.9 and 692,654.1 before),
+# so these are the counts of the search
+OPS_PER_TABLE = {"tables_kernel": 4769.1, "fisher_kernel": 50573.6}
 VALU_JSON = os.path.join(ROOT, "profiles", "gen_kernels_valu_262144x4096.json")
 
 
@@ -252,7 +253,7 @@ def valu_summary(valu_csv, bench_log):
     for name, prefix in [("f64_uniform", "gen_kernel<0, 0,"), ("f32_uniform", "gen_kernel<0, 1,"),
                          ("f64_normal", "gen_kernel<1, 0,"), ("f64_exponential", "gen_kernel<2, 0,"),
                          ("f32_normal", "gen_kernel<1, 1,"), ("f32_exponential", "gen_kernel<2, 1,")]:
-        put(name, biggest(lambda k, p=prefix: p in k), N, f"{S_STREAMS} streams x {PER_STREAM} draws, per draw")
+        put(name, biggest(lambda k, p=prefix: p in k or p.replace("gen_", "gen_column_") in k), N, f"{S_STREAMS} streams x {PER_STREAM} draws, per draw")
     put("tables_kernel", biggest(lambda k: "tables_kernel" in k), 1_000_000,
         "10^6 tables of the CFG4 mix, per table")
     put("fisher_kernel", biggest(lambda k: "fisher_kernel" in k), 10027008,
