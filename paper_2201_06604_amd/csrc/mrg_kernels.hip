@@ -1114,8 +1114,14 @@ void plan_generate(GenLaunch& L) {
     const uint64_t units_max = L.dist == kNormal ? (cnt_max + 1) / 2 : cnt_max;
     const uint64_t n_sblk = (static_cast<uint64_t>(L.S) + 64ull * L.spl - 1) / (64ull * L.spl);
     if (!L.chunk) {
-        // chunk for about t.waves waves, at least t.min_units units each
-        uint64_t w = (t.waves + n_sblk - 1) / n_sblk;
+        // chunk for about t.waves waves, at least t.min_units units each.  Rows in
+        // step that share lines: below 1,024 stream blocks the wide blocks of one
+        // round come out unevenly over the CUs, and many shorter chunks fill them
+        // (fp32 uniforms, 2^29 to 2^30 draws of 2,252 / 10,007 / 100,003 streams: 817
+        // / 987 / 902 us at 2,048 waves, 689 / 908 / 1,126 at 32,768)
+        uint64_t waves = t.waves;
+        if (!cfg_given && t.lock && !L.nontemporal && n_sblk < 1024 && waves < 32768) waves = 32768;
+        uint64_t w = (waves + n_sblk - 1) / n_sblk;
         const uint64_t w_cap = (units_max + t.min_units - 1) / t.min_units;
         if (w > w_cap) w = w_cap;
         if (w < 1) w = 1;

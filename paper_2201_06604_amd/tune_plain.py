@@ -99,7 +99,10 @@ def resolve(entry, S, n, dist, dtype):
     cnt_max = q + (1 if r else 0)
     units_max = (cnt_max + 1) // 2 if dist == NORMAL else cnt_max
     n_sblk = -(-S // (64 * spl))
-    w = -(-entry["waves"] // n_sblk)
+    waves = entry["waves"]
+    if entry["lock"] and S * esz % 128 and n_sblk < 1024:
+        waves = max(waves, 32768)
+    w = -(-waves // n_sblk)
     w = min(w, -(-units_max // entry["min_units"]))
     w = max(w, 1)
     chunk = max(1, -(-units_max // w))
