@@ -56,3 +56,9 @@ def test_columns_of_several_streams_a_lane(spl, xcd):
 def test_automatic_shapes_and_one_chunk_agree(n):
     for S in (64, 1001, 16384, 100003):
         check(P.MRG_GEN_MRG32K3A, S, n, KINDS, None, calls=1)
+
+
+# rows in step that share lines: 16, 1,023 and 1,024 stream blocks, where the aim changes
+@pytest.mark.parametrize("S", [1001, 65471, 65473])
+def test_rows_in_step_and_one_chunk_agree(S):
+    check(P.MRG_GEN_MRG32K3A, S, (1 << 26) + 12345, KINDS, None, calls=1)
