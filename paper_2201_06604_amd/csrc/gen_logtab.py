@@ -1,4 +1,4 @@
-"""Write mrg_logtab.h: the 512-entry table of neg2log_unit (mrg_engine.h).
+"""Write mrg_logtab.h: the 512-entry table of scaled_log_unit (mrg_engine.h).
 
     python paper_2201_06604_amd/csrc/gen_logtab.py
 
@@ -61,7 +61,7 @@ def entries():
 
 def main():
     rows = [f"    {{{r.hex()}, {hi.hex()}}},  // j = {j}" for j, (r, hi) in enumerate(entries())]
-    text = """// mrg_logtab.h -- table of neg2log_unit (mrg_engine.h): for interval j of the
+    text = """// mrg_logtab.h -- table of scaled_log_unit (mrg_engine.h): for interval j of the
 // mantissa m in [1/2, 1) (m in [1/2 + j/1024, 1/2 + (j+1)/1024)), -2 R and
 // 2 log(R), R near the reciprocal of the interval's midpoint and chosen so that
 // log(R) lies within 2^-63 of the multiple of 2^-48 stored (R = 1 for the last

@@ -216,7 +216,7 @@ static mrg_status generate_shape(mrg_generator gen, size_t n_streams, uint64_t n
     L.r = static_cast<uint32_t>(n % n_streams);
     L.dist = static_cast<int>(dist);
     L.dtype = static_cast<int>(dtype);
-    L.param = dist == MRG_EXPONENTIAL ? 0.5 / param : 1.0;
+    L.param = dist == MRG_EXPONENTIAL ? 1.0 / param : 1.0;
     if (gen == MRG_GEN_MRG31K3P) L.arith = kArith31;  // its own engine; cfg->arith applies to MRG32k3a
     return ok();
 }
@@ -307,7 +307,7 @@ mrg_status mrg_generate_paper(mrg_generator gen, mrg_stream* dev, size_t n_strea
     L.G1 = g1size;
     L.dist = static_cast<int>(dist);
     L.dtype = static_cast<int>(dtype);
-    L.param = dist == MRG_EXPONENTIAL ? 0.5 / param : 1.0;
+    L.param = dist == MRG_EXPONENTIAL ? 1.0 / param : 1.0;
     plan_paper(L, gid(gen));
     hipError_t e = launch_paper(L, gid(gen), stream);
     if (e != hipSuccess) return hip_fail(e, "paper-geometry launch");

@@ -298,7 +298,7 @@ mrg_status build(mrg_batch_plan& P) {
         L.arith = kArithF64;
         L.nontemporal = 0;  // batch tiles store with ordinary stores
         L.block = kBatchBlock;
-        L.param = q.dist == MRG_EXPONENTIAL ? 0.5 / q.param : 1.0;
+        L.param = q.dist == MRG_EXPONENTIAL ? 1.0 / q.param : 1.0;
         const int esz = static_cast<int>(esz_of(q.dtype));
         const bool plain = q.dist == MRG_UNIFORM || q.dist == MRG_RAW;
         // uniform/raw tiles store up to 16 bytes per lane (4-byte outputs: 1 or

@@ -222,7 +222,7 @@ __device__ __forceinline__ double sqrt_radius(double x) {
     return __builtin_fma(d, h, g);
 }
 
-// The tables of neg2log_unit (mrg_logtab.h) and sincospi_unit
+// The tables of scaled_log_unit (mrg_logtab.h) and sincospi_unit
 // (mrg_sincostab.h) in LDS: every kernel whose code evaluates a transform
 // stages what it reads once per block with stage_tables() (all threads, then
 // a barrier) before any call.
@@ -237,9 +237,19 @@ __device__ __forceinline__ double sqrt_radius(double x) {
 // and their substream step 28.0 -> 26.5 us, the paper's 10^8 MRG31k3p normals
 // 205 -> 192 us.  Three quarters of an fp64 normal launch is VALU issue.
 typedef double double2v __attribute__((ext_vector_type(2)));
+constexpr LogTable halved(LogTable t) {
+    for (auto& e : t.e) {
+        e[0] *= 0.5;
+        e[1] *= 0.5;
+    }
+    return t;
+}
 static __constant__ LogTable g_logtab = kLogTable;
+static __constant__ LogTable g_logtab_half = halved(kLogTable);
 static __constant__ SinCosTable g_sincostab = kSinCosTable;
 
+// The log table of SCALE (1 or 2): -SCALE R and SCALE log(R) of every entry.
+template <int SCALE>
 __device__ __forceinline__ double2v* log_table_lds() {
     __shared__ double2v tab[kLogTabN];
     return tab;
@@ -265,10 +275,11 @@ __device__ __forceinline__ void stage_pairs(double2v* dst, const double (*src)[2
     }
 }
 
-enum { kStageLog = 0, kStageNormalF32 = 1, kStageNormal = 2 };
+enum { kStageExponential = 0, kStageNormalF32 = 1, kStageNormal = 2, kStageAll = 3 };
 template <int WHAT>
 __device__ __forceinline__ void stage_tables() {
-    stage_pairs<kLogTabN>(log_table_lds(), g_logtab.e);
+    if constexpr (WHAT == kStageExponential || WHAT == kStageAll) stage_pairs<kLogTabN>(log_table_lds<1>(), g_logtab_half.e);
+    if constexpr (WHAT >= kStageNormalF32) stage_pairs<kLogTabN>(log_table_lds<2>(), g_logtab.e);
     if constexpr (WHAT >= kStageNormalF32) stage_pairs<kSinCosTabN>(sincos_table_lds(), g_sincostab.hi);
     if constexpr (WHAT >= kStageNormal) stage_pairs<kSinCosTabN>(sincos_table_lds() + kSinCosTabN, g_sincostab.lo);
     __syncthreads();
@@ -316,33 +327,40 @@ __device__ __forceinline__ void sincospi_unit(double t, double* sp, double* cp) 
 constexpr double kLn2Hi = 6.93147180369123816490e-01;  // ln 2 to 32 bits: k * hi exact
 constexpr double kLn2Lo = 1.90821492927058770002e-10;  // ln 2 - hi
 
-// -2 log(u) for the generators' uniforms, u in [2^-33, 1) -- never zero,
-// subnormal, negative or non-finite -- by table: u = m 2^k with m in [1/2, 1);
-// the top 9 fraction bits of m pick an interval of width 1/1024 whose entry
-// holds -2 R, R near 1/m (R = 1 on the last interval), and 2 log(R) (within
-// 2^-62, and 2^-54 of the result).  s = 2 - 2 m R = -2 t with |t| <= 2^-10
-// (1 + 2^-4), and -2 log(m) = 2 log(R) - 2 log1p(t), where
-// log1p(t) = t + t^2 P(t) through t^5 with the t^6 term folded into P by
-// Chebyshev's polynomial (2^-55 of t is left at |t| = 2^-10) and
-// -2 log1p(t) = s + s^2 Q(s).  -2 k ln2_hi + 2 log(R) is exact (multiples of
-// 2^-31 and 2^-47 below 2^6).  Near u = 1 (k = 0, R = 1) the result is
-// s + s^2 Q(s) alone, accurate relative to its own size.  The factor -2, the
-// radius's, is in the tables and constants; an exponential takes half of it
-// with its rate.  15 instructions and one LDS load.
-__device__ __forceinline__ double neg2log_unit(double u) {
+// -SCALE log(u), SCALE 1 (exponentials) or 2 (the radius), for the generators'
+// uniforms, u in [2^-33, 1) -- never zero, subnormal, negative or non-finite --
+// by table: u = m 2^k with m in [1/2, 1); the top 9 fraction bits of m pick an
+// interval of width 1/1024 whose entry holds, for SCALE 2, -2 R, R near 1/m
+// (R = 1 on the last interval), and 2 log(R) (within 2^-62, and 2^-54 of the
+// result).  s = 2 - 2 m R = -2 t with |t| <= 2^-10 (1 + 2^-4), and
+// -2 log(m) = 2 log(R) - 2 log1p(t), where log1p(t) = t + t^2 P(t) through t^5
+// with the t^6 term folded into P by Chebyshev's polynomial (2^-55 of t is left
+// at |t| = 2^-10) and -2 log1p(t) = s + s^2 Q(s).  -2 k ln2_hi + 2 log(R) is
+// exact (multiples of 2^-31 and 2^-47 below 2^6).  Near u = 1 (k = 0, R = 1) the
+// result is s + s^2 Q(s) alone, accurate relative to its own size.  15
+// instructions and one LDS load.
+//
+// SCALE 1 has half of everything: table, constants and coefficients differ by
+// powers of two, so its result is exactly half of SCALE 2's.  With the factor in
+// the rate instead, rates above 2^1022, whose reciprocal is subnormal, would lose
+// the bit that half of it has no room for.
+template <int SCALE>
+__device__ __forceinline__ double scaled_log_unit(double u) {
+    static_assert(SCALE == 1 || SCALE == 2, "tables of two scales");
+    constexpr double f = 2.0 / SCALE;  // s is 1/f of SCALE 2's
     const int k = __builtin_amdgcn_frexp_exp(u);
     const double m = __builtin_amdgcn_frexp_mant(u);  // [1/2, 1)
     static_assert(kLogTabN == 512, "the index takes the top 9 fraction bits of m");
     const uint32_t j = (static_cast<uint32_t>(__double2hiint(m)) >> 11) & (kLogTabN - 1);
-    const double2v e = log_table_lds()[j];
-    const double s = __builtin_fma(m, e.x, 2.0);
-    double q = 0x1.999999999999ap-7;                   // 1/80
-    q = __builtin_fma(q, s, 0x1.00000aaaaaaabp-5);     // 1/32 + 2^-20/48
-    q = __builtin_fma(q, s, 0x1.5555555555555p-4);     // 1/12
-    q = __builtin_fma(q, s, 0x1.ffffffffffeabp-3);     // 1/4 - 2^-40/96
+    const double2v e = log_table_lds<SCALE>()[j];
+    const double s = __builtin_fma(m, e.x, static_cast<double>(SCALE));
+    double q = 0x1.999999999999ap-7 * f * f * f * f;               // 1/80
+    q = __builtin_fma(q, s, 0x1.00000aaaaaaabp-5 * f * f * f);     // 1/32 + 2^-20/48
+    q = __builtin_fma(q, s, 0x1.5555555555555p-4 * f * f);         // 1/12
+    q = __builtin_fma(q, s, 0x1.ffffffffffeabp-3 * f);             // 1/4 - 2^-40/96
     const double kd = static_cast<double>(k);
-    const double lo = __builtin_fma(s * s, q, kd * (-2.0 * kLn2Lo));
-    return __builtin_fma(kd, -2.0 * kLn2Hi, e.y) + (s + lo);
+    const double lo = __builtin_fma(s * s, q, kd * (-SCALE * kLn2Lo));
+    return __builtin_fma(kd, -SCALE * kLn2Hi, e.y) + (s + lo);
 }
 
 // ----------------------------------------------- transforms for fp32 output
@@ -355,20 +373,22 @@ __device__ __forceinline__ double neg2log_unit(double u) {
 // float is then under 4e-7 of max(|value|, 1), against the 1e-6 fp32
 // tolerance.
 
-// -2 log(u) by neg2log_unit's table: log1p(t) through t^3 (the next term,
+// -SCALE log(u) by scaled_log_unit's table: log1p(t) through t^3 (the next term,
 // t^4/4 < 2^-41, is below 2^-31 of any result outside the last interval, where
 // |log u| >= 2^-10, and of t on the last one); the low bits of ln 2 are left
 // out (below 2^-31 of the result).  Near u = 1 (k = 0, R = 1) the result is
-// -2 log1p(t) alone, accurate relative to its own size.
-__device__ __forceinline__ double neg2log_unit_f32out(double u) {
+// -SCALE log1p(t) alone, accurate relative to its own size.
+template <int SCALE>
+__device__ __forceinline__ double scaled_log_unit_f32out(double u) {
+    constexpr double f = 2.0 / SCALE;
     const int k = __builtin_amdgcn_frexp_exp(u);
     const double m = __builtin_amdgcn_frexp_mant(u);  // [1/2, 1)
     const uint32_t j = (static_cast<uint32_t>(__double2hiint(m)) >> 11) & (kLogTabN - 1);
-    const double2v e = log_table_lds()[j];
-    const double s = __builtin_fma(m, e.x, 2.0);
-    const double q = __builtin_fma(s * s, __builtin_fma(s, 1.0 / 12.0, 0.25), s);
+    const double2v e = log_table_lds<SCALE>()[j];
+    const double s = __builtin_fma(m, e.x, static_cast<double>(SCALE));
+    const double q = __builtin_fma(s * s, __builtin_fma(s, f * f / 12.0, f / 4.0), s);
     constexpr double kLn2 = 6.93147180559945286227e-01;
-    return __builtin_fma(static_cast<double>(k), -2.0 * kLn2, e.y) + q;
+    return __builtin_fma(static_cast<double>(k), -SCALE * kLn2, e.y) + q;
 }
 
 // sqrt(x) for the radius argument, x in [2^-32, 47]: the hardware reciprocal

@@ -23,7 +23,7 @@ struct GenLaunch {
     uint32_t r;          // n mod S
     uint32_t chunk;      // units (draws; normal: pairs) per work-item
     uint32_t n_chunks;   // work-items per stream
-    double param;        // 1/(2 rate) for exponentials (times -2 log u)
+    double param;        // 1/rate for exponentials
     int dist, dtype, arith, block, nontemporal;
     int spl;             // streams per lane (1, 2, 4); 0 = automatic
     int xcd;             // 1 = XCD-contiguous block order
@@ -160,7 +160,7 @@ struct PaperLaunch {
     uint32_t cols_per;   // and cols_per of each row's visits (cols_per < all only with rows_per = 1) ...
     uint32_t n_cb;       // ... in n_cb column blocks
     int dist, dtype;
-    double param;        // 1/(2 rate) for exponentials (times -2 log u)
+    double param;        // 1/rate for exponentials
     int paired;          // normals: X and Y of every pair may leave in one aligned store
 };
 void plan_paper(PaperLaunch& L, int gen);

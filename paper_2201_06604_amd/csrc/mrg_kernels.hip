@@ -121,7 +121,7 @@ __device__ __forceinline__ constexpr double norm_of() {
 
 // The stored value of one uniform / raw / exponential draw.
 template <int DIST, int DTYPE, int G, typename Z>
-__device__ __forceinline__ typename ElemOf<DTYPE>::T value1(Z z, double half_inv_rate) {
+__device__ __forceinline__ typename ElemOf<DTYPE>::T value1(Z z, double inv_rate) {
     if constexpr (DIST == kRaw) {
         return to_u32(z);
     } else if constexpr (DIST == kUniform && DTYPE == kF32) {
@@ -129,8 +129,8 @@ __device__ __forceinline__ typename ElemOf<DTYPE>::T value1(Z z, double half_inv
     } else {
         double u = to_f64(z) * norm_of<G>();
         if constexpr (DIST == kExponential) {
-            if constexpr (DTYPE == kF64) return neg2log_unit(u) * half_inv_rate;
-            else return static_cast<float>(neg2log_unit_f32out(u) * half_inv_rate);
+            if constexpr (DTYPE == kF64) return scaled_log_unit<1>(u) * inv_rate;
+            else return static_cast<float>(scaled_log_unit_f32out<1>(u) * inv_rate);
         } else {
             return u;
         }
@@ -140,7 +140,7 @@ __device__ __forceinline__ typename ElemOf<DTYPE>::T value1(Z z, double half_inv
 // What a kernel of one distribution and type stages.
 template <int DIST, int DTYPE>
 __device__ __forceinline__ void stage_for() {
-    if constexpr (DIST == kExponential) stage_tables<kStageLog>();
+    if constexpr (DIST == kExponential) stage_tables<kStageExponential>();
     if constexpr (DIST == kNormal) stage_tables<DTYPE == kF64 ? kStageNormal : kStageNormalF32>();
 }
 
@@ -154,10 +154,10 @@ __device__ __forceinline__ void box_muller(Z z1, Z z2, double& x, double& y) {
     const double t = to_f64(z2) * (2.0 * norm_of<G>());
     double r, s, c;
     if constexpr (DTYPE == kF64) {
-        r = sqrt_radius(neg2log_unit(u1));
+        r = sqrt_radius(scaled_log_unit<2>(u1));
         sincospi_unit(t, &s, &c);
     } else {
-        r = sqrt_radius_f32out(neg2log_unit_f32out(u1));
+        r = sqrt_radius_f32out(scaled_log_unit_f32out<2>(u1));
         sincospi_unit_f32out(t, &s, &c);
     }
     x = r * c;
@@ -299,7 +299,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
         e[i].load(x[i]);
     }
 
-    const double half_inv_rate = L.param;
+    const double inv_rate = L.param;
     const uint64_t rowstep = static_cast<uint64_t>(S) * ESZ;
     const uint64_t rest = static_cast<uint64_t>(S - first) * ESZ;
     const uint32_t nrec = rest > 0xffffffffull ? 0xffffffffu : static_cast<uint32_t>(rest);
@@ -398,7 +398,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
             Pack<T, SPL> p;
 #pragma unroll
             for (int i = 0; i < SPL; ++i)
-                p.v[i] = value1<DIST, DTYPE, G>(e[i].template step<decltype(step)::value>(kr), half_inv_rate);
+                p.v[i] = value1<DIST, DTYPE, G>(e[i].template step<decltype(step)::value>(kr), inv_rate);
             store_row(row, p);
             row += rowstep;
             row_done();
@@ -412,7 +412,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
         for (; k < kend; ++k) {
             Pack<T, SPL> p;
 #pragma unroll
-            for (int i = 0; i < SPL; ++i) p.v[i] = value1<DIST, DTYPE, G>(e[i].step_rot(kr), half_inv_rate);
+            for (int i = 0; i < SPL; ++i) p.v[i] = value1<DIST, DTYPE, G>(e[i].step_rot(kr), inv_rate);
             store_row(row, p);
             row += rowstep;
         }
@@ -421,7 +421,7 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
 #pragma unroll
             for (int i = 0; i < SPL; ++i)
                 if (k < units[i])
-                    store_value(row, i, value1<DIST, DTYPE, G>(e[i].step_rot(kr), half_inv_rate));
+                    store_value(row, i, value1<DIST, DTYPE, G>(e[i].step_rot(kr), inv_rate));
             row += rowstep;
         }
     }
@@ -678,7 +678,7 @@ __device__ __forceinline__ uint32_t home_rank(const BatchLaunch& B, int cls) {
 // then helps the other classes until every queue is empty.  The three loops
 // run one after another, so their register live ranges never overlap.
 __global__ void __launch_bounds__(256) batch_kernel(BatchLaunch B) {
-    stage_tables<kStageNormal>();
+    stage_tables<kStageAll>();
     constexpr uint32_t kNone = 0xffffffffu;
     if (blockIdx.x == 0 && threadIdx.x < 64) B.head->t_start = __builtin_amdgcn_s_memrealtime();
     if (blockIdx.x < B.block_lo[1]) {
@@ -774,7 +774,7 @@ __device__ __forceinline__ uint32_t tile_iters(const BatchLaunch& B, const Batch
 // SIMD, where the code of every kind together allows three.
 template <bool NARROW>
 __device__ __forceinline__ void gang_loop(const BatchLaunch& B) {
-    stage_tables<kStageNormal>();
+    stage_tables<kStageAll>();
     __shared__ uint32_t next_gang;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t one = lane == 0 ? 1u : 0u;
@@ -1446,7 +1446,7 @@ __global__ void __launch_bounds__(256) paper_kernel(PaperLaunch L) {
         eb.load(x);
     }
     T* out = static_cast<T*>(L.out);
-    const double half_inv_rate = L.param;
+    const double inv_rate = L.param;
     // One visit: step P of three (the register ring returns home), -1: a step
     // that rotates it.  PAIR: X and Y leave in one store.
     const auto visit = [&](auto step, auto pair, T* at) {
@@ -1468,7 +1468,7 @@ __global__ void __launch_bounds__(256) paper_kernel(PaperLaunch L) {
                 __builtin_nontemporal_store(narrow<DTYPE>(yv), at + 1);
             }
         } else {
-            __builtin_nontemporal_store(value1<DIST, DTYPE, G>(next(ea), half_inv_rate), at);
+            __builtin_nontemporal_store(value1<DIST, DTYPE, G>(next(ea), inv_rate), at);
         }
     };
     // Three visits an iteration save the register rotation (fp64 normals of 10^4 x

@@ -1,7 +1,7 @@
 // mrg_selfcheck.hip -- diagnostics: the library's own transcendentals against
 // the HIP device math library over whole input ranges.
 //
-// The normal and exponential transforms use neg2log_unit, sqrt_radius and
+// The normal and exponential transforms use scaled_log_unit, sqrt_radius and
 // sincospi_unit (mrg_engine.h) instead of the general library functions:
 // they leave out range reduction and special cases that the generators'
 // uniforms can never reach.  mrg_transform_accuracy evaluates one of them and
@@ -35,10 +35,10 @@ template <int G>
 __device__ __forceinline__ uint64_t distance_at(int fn, uint64_t z) {
     constexpr double norm = G == kGen32k3a ? kNorm : kNorm31;
     const double u = static_cast<double>(z) * norm;
-    if (fn == MRG_CHECK_LOG) return ulp_distance(-0.5 * neg2log_unit(u), log(u));
-    if (fn == MRG_CHECK_LOG_F32OUT) return ulp_distance(-0.5 * neg2log_unit_f32out(u), log(u));
+    if (fn == MRG_CHECK_LOG) return ulp_distance(-scaled_log_unit<1>(u), log(u));
+    if (fn == MRG_CHECK_LOG_F32OUT) return ulp_distance(-scaled_log_unit_f32out<1>(u), log(u));
     if (fn == MRG_CHECK_SQRT || fn == MRG_CHECK_SQRT_F32OUT) {
-        const double x = neg2log_unit(u);  // the Box-Muller radius argument
+        const double x = scaled_log_unit<2>(u);  // the Box-Muller radius argument
         return ulp_distance(fn == MRG_CHECK_SQRT ? sqrt_radius(x) : sqrt_radius_f32out(x), sqrt(x));
     }
     // the Box-Muller angle argument 2u, formed as the kernels form it
@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(64) accuracy_clear_kernel(unsigned long long* 
 // among equal ones, the largest z.
 template <int G>
 __global__ void __launch_bounds__(256) accuracy_kernel(int fn, uint64_t z0, uint64_t z1, unsigned long long* res) {
-    stage_tables<kStageNormal>();
+    stage_tables<kStageAll>();
     __shared__ unsigned long long bins[kAccuracyBins];
     __shared__ unsigned long long worst;
     if (threadIdx.x < kAccuracyBins) bins[threadIdx.x] = 0;

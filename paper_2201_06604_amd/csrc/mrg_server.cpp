@@ -348,7 +348,7 @@ hipError_t mrg_server::enqueue(Lane& L, const std::vector<PlanReq>& reqs, const 
         G.r = static_cast<uint32_t>(reqs[0].q.n % G.S);
         G.dist = static_cast<int>(reqs[0].q.dist);
         G.dtype = static_cast<int>(reqs[0].q.dtype);
-        G.param = reqs[0].q.dist == MRG_EXPONENTIAL ? 0.5 / reqs[0].q.param : 1.0;
+        G.param = reqs[0].q.dist == MRG_EXPONENTIAL ? 1.0 / reqs[0].q.param : 1.0;
         G.offset = reqs[0].offset;
         G.no_writeback = 1;
         plan_generate(G);
@@ -402,7 +402,7 @@ bool mrg_server::launch_plain() {
     G.r = static_cast<uint32_t>(t.n % S);
     G.dist = static_cast<int>(t.dist);
     G.dtype = static_cast<int>(t.dtype);
-    G.param = t.dist == MRG_EXPONENTIAL ? 0.5 / t.param : 1.0;
+    G.param = t.dist == MRG_EXPONENTIAL ? 1.0 / t.param : 1.0;
     G.offset = t.offset;
     G.no_writeback = 1;
     plan_generate(G);
