@@ -23,6 +23,8 @@
 // Both produce identical integers; tests check both against the oracle.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -441,6 +443,15 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
     }
 }
 
+// The logical block of physical block `lin` of `total`: the physical blocks lin mod
+// 8 of one XCD take consecutive ones.  For any total, the first total mod 8 XCDs one
+// more: with the remap left out where 8 does not divide the blocks, 2^28 fp32
+// uniforms of 30,011 streams took 285 us in step, 215 with it.
+__device__ __forceinline__ uint32_t xcd_order(uint32_t lin, uint32_t total) {
+    const uint32_t x = lin % 8, more = total % 8;
+    return x * (total / 8) + (x < more ? x : more) + lin / 8;
+}
+
 // LOCK: the waves of a block pass a barrier after each row of the main
 // loops (three per unrolled iteration), so a block writes 64*SPL*waves
 // consecutive elements of a row at once.  All waves of a block run the same
@@ -455,9 +466,7 @@ __global__ void __launch_bounds__(1024) gen_kernel(GenLaunch L) {
     // contiguous runs of every row; blocks are dealt to the 8 XCDs in turn.
     uint32_t bx = blockIdx.x, by = blockIdx.y;
     if (L.xcd) {
-        const uint32_t total = gridDim.x * gridDim.y;
-        uint32_t lin = blockIdx.x + blockIdx.y * gridDim.x;
-        lin = (lin % 8) * (total / 8) + lin / 8;  // host guarantees total % 8 == 0
+        const uint32_t lin = xcd_order(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
         bx = lin % gridDim.x;
         by = lin / gridDim.x;
     }
@@ -1073,20 +1082,106 @@ hipError_t launch_advance(int gen, uint32_t* streams, uint64_t n, uint64_t steps
     return hipGetLastError();
 }
 
-// The tuned shape of a call: kind (dist, dtype), size class and half of its
-// draw count, and whether its rows start on 128-byte lines.
-static const TunedShape& tuned_shape(const GenLaunch& L) {
-    int kind;
+// The output kind of a call, an index of kTuned.
+static int tuned_kind(const GenLaunch& L) {
     switch (L.dist) {
-        case kUniform: kind = L.dtype == kF64 ? 0 : 1; break;
-        case kRaw: kind = 2; break;
-        case kNormal: kind = L.dtype == kF64 ? 3 : 4; break;
-        default: kind = L.dtype == kF64 ? 5 : 6; break;
+        case kUniform: return L.dtype == kF64 ? 0 : 1;
+        case kRaw: return 2;
+        case kNormal: return L.dtype == kF64 ? 3 : 4;
+        default: return L.dtype == kF64 ? 5 : 6;
     }
+}
+
+constexpr uint64_t kOneWave = 1024;  // waves of a grid of one wave a SIMD
+
+// The tuned shape of a call: its kind, size class and half of its draw count, and
+// whether its rows start on 4 KB pages, on 128-byte lines or anywhere.  The shapes of
+// one wave a SIMD in all (kOneWave) are for the stream counts whose stream blocks
+// divide it, not into columns of two: the others of rows on pages take the shape of
+// rows on lines (2^28 fp32 uniforms of 81,920, 99,328 and 131,072 streams 238, 239 and
+// 258 us in one wave a SIMD, 193, 199 and 193 in many).
+static const TunedShape& tuned_shape(const GenLaunch& L) {
     const uint64_t n = L.q * L.S + L.r;
     const int cls = n < (1ull << 18) ? 0 : n < (1ull << 22) ? 1 : n < (1ull << 26) ? 2 : n < (1ull << 29) ? 3 : 4;
-    const int esz = L.dtype == kF64 ? 8 : 4;
-    return kTuned[kind][cls][n >= kTunedHalf[cls] ? 1 : 0][static_cast<uint64_t>(L.S) * esz % 128 ? 1 : 0];
+    const uint64_t row = static_cast<uint64_t>(L.S) * (L.dtype == kF64 ? 8 : 4);
+    const TunedShape* t = kTuned[tuned_kind(L)][cls][n >= kTunedHalf[cls] ? 1 : 0];
+    const int at = row % 128 ? 2 : row % 4096 ? 1 : 0;
+    if (at == 0 && cls >= 3 && t[0].waves == kOneWave && !t[0].lock) {
+        const uint64_t all = kOneWave * 64 * t[0].spl;
+        if (all % L.S || all / L.S == 2) return t[1];
+    }
+    return t[at];
+}
+
+// What a grid costs, in microseconds of the busiest CU: blocks come out evenly over
+// the 256 CUs only by their number, so that CU runs the blocks of the last, perhaps
+// almost empty, round as well, whether they wait for a place or share it.  A SIMD
+// issues at full rate from two waves on, or one of several streams a lane (a lone
+// chain issues every other slot).
+// A chunk costs its units and a start (state read, jump, tables), and a chunked
+// launch its finalize kernel unless it runs in columns.
+constexpr double kCUs = 256.0;
+constexpr double kUnitSlots[kTunedKinds] = {16, 16, 15, 73, 60, 32, 29};  // VALU slots of a unit, by kind
+constexpr double kStartSlots = 256.0;                                     // of a chunk's start
+constexpr double kSlotUs = 1.0 / 2100.0;                                  // 4 SIMDs, 4 cycles a slot, 2.1 GHz
+constexpr double kFinalizeUs = 4.0;
+constexpr uint64_t kGapWaves = 32768;  // aimed at where a row's last block is mostly idle
+constexpr uint64_t kNarrowWaves = 8192;  // and where rows are no more than a few waves wide, in calls of
+constexpr uint64_t kNarrowFrom = 1 << 26;  // this many draws
+constexpr uint64_t kLockFrom = 1536;  // and from which rows in step are worth their barriers
+
+struct ChunkChoice {
+    uint64_t chunk, n_chunks;
+    int wpb;
+    double cost;
+};
+
+static ChunkChoice grid_cost(uint64_t n_sblk, uint64_t units, uint64_t chunks, int wpb, bool lock, double unit_slots,
+                             int spl) {
+    ChunkChoice c;
+    c.chunk = (units + chunks - 1) / chunks;
+    c.n_chunks = (units + c.chunk - 1) / c.chunk;
+    c.wpb = wpb;
+    const double k = static_cast<double>(c.n_chunks);
+    const bool column = !lock && c.n_chunks > 1 && c.n_chunks <= static_cast<uint64_t>(wpb);
+    const double blocks = column ? static_cast<double>(n_sblk) : static_cast<double>((n_sblk + wpb - 1) / wpb) * k;
+    const double waves = std::ceil(blocks / kCUs) * (column ? k : wpb);
+    c.cost = std::max(spl > 1 ? 4.0 : 8.0, waves) * (static_cast<double>(c.chunk) * unit_slots + kStartSlots) * spl * kSlotUs;
+    if (c.n_chunks > 1 && !column) c.cost += kFinalizeUs;
+    return c;
+}
+
+// The chunk count nearest to an aim of `aim` chunks a stream block whose grid costs
+// least, and the block width likewise.  Rows in step on lines they share (`shared`)
+// keep their width, how much of a row a block writes whole, and few chunks.  Rounding the aim up by itself leaves most stream
+// counts with a round of a few blocks: 2^28 fp32 uniforms of 20,032 streams (260
+// blocks of 4 waves) took 313 us, 222 with blocks that fill their rounds.
+static ChunkChoice choose_chunks(uint64_t n_sblk, uint64_t units, uint64_t aim, uint64_t most, int wpb, bool lock,
+                                 bool shared, double unit_slots, int spl) {
+    ChunkChoice best = grid_cost(n_sblk, units, aim, wpb, lock, unit_slots, spl);
+    const auto consider = [&](uint64_t chunks, int w, double handicap) {
+        if (chunks < 1 || chunks > most) return;
+        ChunkChoice c = grid_cost(n_sblk, units, chunks, w, lock, unit_slots, spl);
+        // the tuned aim and width, which stand for more than this cost, are kept where
+        // little is gained
+        const double far = static_cast<double>(chunks) / static_cast<double>(aim);
+        c.cost *= handicap + 0.15 * (far > 1.0 ? far - 1.0 : 1.0 / far - 1.0);
+        if (c.cost < best.cost) best = c;
+    };
+    for (int w = wpb; w >= 1; w /= 2) {
+        const bool whole = static_cast<uint64_t>(w) >= n_sblk;  // rows in one block
+        if (w < wpb && !whole && (shared || w < 4)) break;
+        const uint64_t row = (n_sblk + w - 1) / w;
+        const double handicap = w == wpb ? 1.01 : 1.04;
+        if (row <= 256) {  // the most chunks of m full rounds
+            const uint64_t r = aim * row / 256;
+            for (uint64_t m = std::max<uint64_t>(1, r - r / 3); m <= r + r / 2 + (shared ? 1 : 3) && m < r + 8; ++m)
+                consider(256 * m / row, w, handicap);
+        } else {
+            for (uint64_t k = aim - aim / 3; k <= aim + aim / 2 + (shared ? 2 : 6); ++k) consider(k, w, handicap);
+        }
+    }
+    return best;
 }
 
 void plan_generate(GenLaunch& L) {
@@ -1113,19 +1208,26 @@ void plan_generate(GenLaunch& L) {
     const uint64_t cnt_max = L.q + (L.r ? 1 : 0);
     const uint64_t units_max = L.dist == kNormal ? (cnt_max + 1) / 2 : cnt_max;
     const uint64_t n_sblk = (static_cast<uint64_t>(L.S) + 64ull * L.spl - 1) / (64ull * L.spl);
+    bool chosen = false;
     if (!L.chunk) {
-        // chunk for about t.waves waves, at least t.min_units units each.  Rows in
-        // step that share lines: below 1,024 stream blocks the wide blocks of one
-        // round come out unevenly over the CUs, and many shorter chunks fill them
-        // (fp32 uniforms, 2^29 to 2^30 draws of 2,252 / 10,007 / 100,003 streams: 817
-        // / 987 / 902 us at 2,048 waves, 689 / 908 / 1,126 at 32,768)
-        uint64_t waves = t.waves;
-        if (!cfg_given && t.lock && !L.nontemporal && n_sblk < 1024 && waves < 32768) waves = 32768;
-        uint64_t w = (waves + n_sblk - 1) / n_sblk;
-        const uint64_t w_cap = (units_max + t.min_units - 1) / t.min_units;
-        if (w > w_cap) w = w_cap;
-        if (w < 1) w = 1;
-        const uint64_t c = (units_max + w - 1) / w;
+        // chunks for about t.waves waves, of at least t.min_units units each
+        const uint64_t most = std::max<uint64_t>(1, (units_max + t.min_units - 1) / t.min_units);
+        const uint64_t wide = static_cast<uint64_t>(L.block) / 64;
+        const bool shared = !cfg_given && t.lock && !L.nontemporal;
+        // in step on shared lines, blocks far from full come out evenly in many short chunks only
+        const bool gaps = shared && 5 * n_sblk < 4 * ((n_sblk + wide - 1) / wide * wide);
+        uint64_t aim = gaps ? std::max<uint64_t>(t.waves, kGapWaves) : t.waves;
+        if (!cfg_given && !t.lock && n_sblk < 4 && L.q * L.S >= kNarrowFrom) aim = std::max<uint64_t>(aim, kNarrowWaves);
+        uint64_t w = std::min(most, (aim + n_sblk - 1) / n_sblk);
+        uint64_t c = (units_max + w - 1) / w;
+        // more waves than the CUs hold at one a SIMD: the number of blocks matters
+        if (!cfg_given && n_sblk * w > kOneWave) {
+            const ChunkChoice e = choose_chunks(n_sblk, units_max, w, most, L.block / 64, t.lock != 0,
+                                                shared, kUnitSlots[tuned_kind(L)], L.spl);
+            c = e.chunk;
+            L.block = 64 * e.wpb;
+            chosen = true;
+        }
         L.chunk = static_cast<uint32_t>(c > 0xffffffffull ? 0xffffffffull : (c ? c : 1));
     }
     uint64_t nch = units_max ? (units_max + L.chunk - 1) / L.chunk : 0;
@@ -1135,23 +1237,22 @@ void plan_generate(GenLaunch& L) {
         nch = (units_max + c - 1) / c;
     }
     L.n_chunks = static_cast<uint32_t>(nch);
-    // Lockstep rows: once the grid fills the chip (two waves per SIMD), the
+    // Lockstep rows: once the grid fills the chip (six waves a CU and more), the
     // waves of a block writing each row together beat free-running waves where
     // stores bound the call (65,536 x 4,096 fp64 uniforms: 457 -> 303 us) and
     // where neighbouring waves share lines (262,143 x 4,096: fp64 normals 3.68 ->
     // 1.76 ms, fp32 uniforms 2.16 -> 0.77 ms); smaller grids are latency-bound
-    if (!cfg_given && t.lock) L.lock = n_sblk * nch >= 2048;
+    if (!cfg_given && t.lock) L.lock = n_sblk * nch >= kLockFrom && (!L.nontemporal || n_sblk * 64 >= static_cast<uint64_t>(L.block));
     uint64_t wpb = static_cast<uint64_t>(L.block) / 64;
     L.column = !L.lock && nch > 1 && nch <= wpb;
     // Neither rows in step nor a column keeps the waves of a block together:
     // narrow blocks, so that a small grid spreads over more CUs (1,024 streams
     // x 16 fp64 uniforms: 4.4 us in one block of 16 waves, 2.9 in four of 4)
-    if (!cfg_given && !L.lock && !L.column && n_sblk * nch < 2048 && L.block > 256) {
+    if (!cfg_given && !chosen && !L.lock && !L.column && n_sblk * nch < 2048 && L.block > 256) {
         L.block = 256;
         wpb = 4;
     }
-    const uint64_t blocks = L.column ? n_sblk : (n_sblk + wpb - 1) / wpb * nch;
-    if (L.xcd && blocks % 8) L.xcd = 0;  // the remap needs a multiple of 8 blocks
+    if (L.xcd && L.column && n_sblk % 8) L.xcd = 0;  // a column's remap needs a multiple of 8 blocks
 }
 
 template <int DIST, int DTYPE, int ARITH, int SPL, bool NT, bool LOCK>
@@ -1222,9 +1323,7 @@ template <typename T, int SPL, bool NT, bool LOCK>
 __global__ void __launch_bounds__(1024) store_ceiling_kernel(GenLaunch L, T value) {
     uint32_t bx = blockIdx.x, by = blockIdx.y;
     if (L.xcd) {
-        const uint32_t total = gridDim.x * gridDim.y;
-        uint32_t lin = blockIdx.x + blockIdx.y * gridDim.x;
-        lin = (lin % 8) * (total / 8) + lin / 8;
+        const uint32_t lin = xcd_order(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
         bx = lin % gridDim.x;
         by = lin / gridDim.x;
     }
