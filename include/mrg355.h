@@ -423,9 +423,10 @@ mrg_status mrg_batch_request_times(const mrg_batch_plan* plan, const void* dev_w
  * the one before is skipped) of the plan on the GPU with its own requests,
  * in `dev_workspace` (capacity `workspace_bytes`; shapes whose workspace would
  * not fit are skipped: mrg_batch_autotune_workspace_size gives the capacity
- * that fits every candidate), keep
- * the fastest in the plan (re-cut and uploaded again) and report it in
- * `best` / `best_ms` (optional).  Every request's stream records are saved to
+ * that fits every candidate), report
+ * the fastest in `best` and keep it in the plan (re-cut and uploaded again), unless
+ * the plan's own shape, timed as well, is faster still and stays; `best_ms` is the
+ * time of what the plan then runs (both optional).  Every request's stream records are saved to
  * host memory first and restored at the end, so the streams are left as they
  * were; the outputs are overwritten.  Synchronises `stream`. */
 mrg_status mrg_batch_autotune(mrg_batch_plan* plan, void* dev_workspace, size_t workspace_bytes,

@@ -538,8 +538,8 @@ class BatchPlan:
         return b.value
 
     def autotune(self, stream=None):
-        """Time the candidate shapes and keep the fastest; the workspace is
-        grown first so that every candidate fits (then uploaded again).  A
+        """Time the candidate shapes and keep the fastest, or the plan's own
+        shape where that is faster than all of them; the workspace is grown first so that every candidate fits (then uploaded again).  A
         graph captured with the previous workspace must be captured again
         after this call, and the plan's tables are re-cut for the chosen shape."""
         need = self.autotune_workspace_size()
