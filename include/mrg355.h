@@ -379,7 +379,9 @@ mrg_status mrg_batch_plan_create(mrg_generator gen, const mrg_request* reqs, siz
 void       mrg_batch_plan_destroy(mrg_batch_plan* plan);
 
 /* Device workspace the caller provides for a plan (256-byte aligned), and
- * the plan's tile count. */
+ * the plan's tile count: stream blocks times chunks, summed over the requests; in
+ * gang mode each class's sum (normals, exponentials, uniforms and raw words) rounded
+ * up to whole gangs. */
 mrg_status mrg_batch_workspace_size(const mrg_batch_plan* plan, size_t* bytes);
 mrg_status mrg_batch_tile_count(const mrg_batch_plan* plan, size_t* tiles);
 

@@ -34,7 +34,7 @@ struct mrg_batch_plan {
     uint32_t gang;  // 1 = class queues of wave tiles; 2, 4, 8 = gangs of that many waves
     std::vector<BatchReq> reqs;
     std::vector<BatchTile> tiles;
-    size_t cut;  // tiles of the cut; in gang mode, each class's padded to whole gangs
+    size_t cut;  // tiles of the cut, in gang mode each class's rounded up to whole gangs: what tile_count reports
     uint32_t tile_lo[kClasses + 1];
     double cls_cost[kClasses];
     uint32_t n_gangs;
@@ -53,6 +53,7 @@ namespace {
 // waves per SIMD.
 constexpr uint32_t kDefaultWavesPerSimd = 4;
 constexpr uint32_t kDefaultGang = 8;
+constexpr uint32_t kLongTile = 256;
 constexpr unsigned kBatchBlock = 256;
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -396,7 +397,7 @@ mrg_status build(mrg_batch_plan& P) {
     P.off_slots = 256;
     P.off_reqs = align_up(P.off_slots + n_req * sizeof(BatchSlot), 256);
     P.off_tiles = align_up(P.off_reqs + n_req * sizeof(BatchReq), 256);
-    P.off_fin_req = align_up(P.off_tiles + (P.gang > 1 ? P.cut : P.tiles.size()) * sizeof(BatchTile), 256);
+    P.off_fin_req = align_up(P.off_tiles + P.tiles.size() * sizeof(BatchTile), 256);
     P.off_fin_pre = align_up(P.off_fin_req + P.fin_req.size() * sizeof(uint32_t), 256);
     P.bytes = align_up(P.off_fin_pre + P.fin_pre.size() * sizeof(uint64_t), 256);
     pack_tables(P);
@@ -584,6 +585,12 @@ mrg_status mrg_batch_plan_create(mrg_generator gen, const mrg_request* reqs, siz
     P->wide = cfg ? cfg->wide_stores : 0;
     P->gang = (cfg && cfg->gang_waves) ? cfg->gang_waves : kDefaultGang;
     mrg_status st = build(*P);
+    // an automatic length may cut shorter tiles than kLongTile, and more of them: not
+    // past what the static workspace holds (mrg_batch_launch_static)
+    if (!st && !(cfg && cfg->tile_units) && P->tile_units < kLongTile && P->bytes > MRG_BATCH_STATIC_WORKSPACE_BYTES) {
+        P->tile_units = kLongTile;
+        st = build(*P);
+    }
     if (st) {
         delete P;
         return st;
