@@ -179,6 +179,7 @@ struct mrg_server {
     std::thread th;
     std::atomic<bool> stop{false};
     std::atomic<uint32_t> callers{0};  // API calls waiting for `mu`
+    std::atomic<uint64_t> served{0};   // and those that have had it
     mrg_status error = MRG_OK;
 
     void loop();
@@ -205,13 +206,15 @@ namespace {
 
 // `mu` for an API call.  The scheduler looks at its lanes in a tight loop, and a
 // thread that wakes up on the mutex finds it taken again: a call announces itself,
-// and the scheduler stays off the mutex until the callers have had it.
+// and the scheduler stays off the mutex until as many calls as were waiting have had
+// it.
 struct CallerLock {
     std::unique_lock<std::mutex> lk;
     explicit CallerLock(mrg_server* s) : lk(s->mu, std::defer_lock) {
         s->callers.fetch_add(1, std::memory_order_relaxed);
         lk.lock();
         s->callers.fetch_sub(1, std::memory_order_relaxed);
+        s->served.fetch_add(1, std::memory_order_relaxed);
     }
 };
 
@@ -430,7 +433,10 @@ bool mrg_server::launch_plain() {
 // arrives within the window is picked up without a thread wake-up.
 constexpr uint64_t kSpinWindowNs = 2000000;
 
-// The longest the scheduler stays off the mutex for API calls that want it.
+// The longest the scheduler stays off the mutex for API calls that want it.  Until none
+// wanted it, instead of until those waiting had had it, every look at the lanes came up
+// to 20 us late where threads poll in a loop: one request of 10,000 normals beside 1, 2,
+// 4 and 8 such threads 42, 48, 50 and 59 us, now 27, 30, 37 and 48 (25 without any).
 constexpr uint64_t kGiveWayNs = 20000;
 
 void mrg_server::loop() {
@@ -438,10 +444,15 @@ void mrg_server::loop() {
     std::unique_lock<std::mutex> lk(mu);
     uint64_t last_active = steady_ns();
     while (!stop.load()) {
-        if (callers.load(std::memory_order_relaxed)) {
+        if (const uint32_t waiting = callers.load(std::memory_order_relaxed)) {
+            // threads that poll in a loop are back before the last of them is through:
+            // what ends the wait is their number, not an empty queue
+            const uint64_t enough = served.load(std::memory_order_relaxed) + waiting;
             lk.unlock();
             const uint64_t until = steady_ns() + kGiveWayNs;
-            while (callers.load(std::memory_order_relaxed) && steady_ns() < until) std::this_thread::yield();
+            while (served.load(std::memory_order_relaxed) < enough && callers.load(std::memory_order_relaxed) &&
+                   steady_ns() < until)
+                std::this_thread::yield();
             lk.lock();
         }
         bool progress = cfg.mode == 0 ? poll_lanes() : poll_plain();
