@@ -354,14 +354,18 @@ typedef struct {
  *                   unless a narrower width leaves fewer lanes idle;
  *                   0 = automatic: 1 in gang mode, 2 otherwise.  In gang
  *                   mode a plan of one-stream tiles runs a kernel holding
- *                   only their code, which fits up to six waves per SIMD
- *                   (the kernel with every width fits three)
+ *                   only their code (and that of two streams a lane, 64 or
+ *                   more apart), which fits five waves per SIMD (the kernel
+ *                   with every width fits three)
  *   gang_waves      1 = every wave takes tiles on its own, from one queue per
  *                   class (normal, exponential, uniform/raw); 2, 4 or 8 = a
- *                   block of that many waves takes a gang of that many tiles
- *                   -- neighbouring stream blocks of one request -- and its
- *                   waves write rows together (a barrier every three rows), from
- *                   one queue that interleaves the classes              */
+ *                   block of that many waves takes a gang of up to that many
+ *                   tiles -- all stream blocks of one request and chunk, two
+ *                   a wave where they outnumber the waves, or those of
+ *                   several requests of one class that leave waves to each
+ *                   other -- and its waves write rows together (a barrier
+ *                   every three rows), from one queue a chiplet that
+ *                   interleaves the classes                             */
 typedef struct {
     uint32_t tile_units;
     uint32_t waves_per_simd;

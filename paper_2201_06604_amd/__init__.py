@@ -539,9 +539,11 @@ class BatchPlan:
 
     def autotune(self, stream=None):
         """Time the candidate shapes and keep the fastest, or the plan's own
-        shape where that is faster than all of them; the workspace is grown first so that every candidate fits (then uploaded again).  A
-        graph captured with the previous workspace must be captured again
-        after this call, and the plan's tables are re-cut for the chosen shape."""
+        shape where that is faster than all of them; the workspace is grown
+        first so that every candidate fits (then uploaded again).  A graph
+        captured with the previous workspace must be captured again after
+        this call, and the plan's tables are re-cut for the chosen shape.
+        Returns (the fastest candidate, milliseconds of what the plan runs)."""
         need = self.autotune_workspace_size()
         if self.workspace is None or self._ws_bytes < need:
             self.alloc_workspace(need)

@@ -156,9 +156,8 @@ void pack_tables(mrg_batch_plan& P) {
 // idle.  A row that two gangs share ends and begins within a 128-byte line
 // unless its start happens to be aligned, and the two halves of that line reach
 // memory from different L2s or at different times, as partial writes: with gangs
-// filled to the last wave (one row in most gangs cut in two) stores alone took
-// 7.4 ms for the 4,096-request mix, with rows cut only above 512 streams 6.2 ms,
-// with whole rows 4.8 ms, and 4.8 ms where every row starts on a line.
+// filled to the last wave (one row in most gangs cut in two) the 4,096-request mix's
+// stores alone took 7.3 ms, with whole rows 5.4 ms.
 //
 // Within each class, tiles go longest first and, among tiles of equal length,
 // in (request, chunk, stream block) order.  The classes' gangs are then merged

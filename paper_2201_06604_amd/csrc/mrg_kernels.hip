@@ -325,8 +325,9 @@ __device__ __forceinline__ void run_chunk(const GenLaunch& L, uint32_t sblk, uin
 
     // Rows in step are also computed one after another: left to itself the compiler
     // brings the next rows' arithmetic before the barrier and stores three rows in
-    // a burst (2^30 fp64 uniforms 1.350 ms, 1.329 with the order kept; 100,003 x
-    // 3,000 fp32 uniforms 303 and 277 us, fp64 exponentials 545 and 527).  The fp32
+    // a burst (2^30 fp64 uniforms 1.350 ms, 1.329 with the order kept, what the longer
+    // step before this one took in any order; 100,003 x 3,000 fp32 uniforms 303 and 277
+    // us, fp64 exponentials 545 and 527).  The fp32
     // transforms, bound by arithmetic, keep the freedom (exponentials 347 and 352).
     constexpr bool kInOrder = LOCK == 3 && (DTYPE != kF32 || DIST == kUniform);
     const auto row_done = [] {
