@@ -1154,11 +1154,12 @@ static ChunkChoice grid_cost(uint64_t n_sblk, uint64_t units, uint64_t chunks, i
 
 // The chunk count nearest to an aim of `aim` chunks a stream block whose grid costs
 // least, and the block width likewise.  Rows in step on lines they share (`shared`)
-// keep their width, how much of a row a block writes whole, and few chunks.  Rounding the aim up by itself leaves most stream
-// counts with a round of a few blocks: 2^28 fp32 uniforms of 20,032 streams (260
+// keep their width, how much of a row a block writes whole, and few chunks; rows that
+// fit in one block keep `least` waves of it.  Rounding the aim up by itself leaves most
+// stream counts with a round of a few blocks: 2^28 fp32 uniforms of 20,032 streams (260
 // blocks of 4 waves) took 313 us, 222 with blocks that fill their rounds.
 static ChunkChoice choose_chunks(uint64_t n_sblk, uint64_t units, uint64_t aim, uint64_t most, int wpb, bool lock,
-                                 bool shared, double unit_slots, int spl) {
+                                 bool shared, int least, double unit_slots, int spl) {
     ChunkChoice best = grid_cost(n_sblk, units, aim, wpb, lock, unit_slots, spl);
     const auto consider = [&](uint64_t chunks, int w, double handicap) {
         if (chunks < 1 || chunks > most) return;
@@ -1171,9 +1172,10 @@ static ChunkChoice choose_chunks(uint64_t n_sblk, uint64_t units, uint64_t aim, 
     };
     for (int w = wpb; w >= 1; w /= 2) {
         const bool whole = static_cast<uint64_t>(w) >= n_sblk;  // rows in one block
-        if (w < wpb && !whole && (shared || w < 4)) break;
+        if (w < wpb && (whole ? w < least : shared || w < 4)) break;
         const uint64_t row = (n_sblk + w - 1) / w;
         const double handicap = w == wpb ? 1.01 : 1.04;
+        if (w < wpb) consider(aim, w, handicap);
         if (row <= 256) {  // the most chunks of m full rounds
             const uint64_t r = aim * row / 256;
             for (uint64_t m = std::max<uint64_t>(1, r - r / 3); m <= r + r / 2 + (shared ? 1 : 3) && m < r + 8; ++m)
@@ -1223,8 +1225,12 @@ void plan_generate(GenLaunch& L) {
         uint64_t c = (units_max + w - 1) / w;
         // more waves than the CUs hold at one a SIMD: the number of blocks matters
         if (!cfg_given && n_sblk * w > kOneWave) {
+            // four waves share the staging of the normals' two tables in calls too short
+            // to spread it (6 M fp32 normals of 64 streams: 23.9 us in blocks of one wave,
+            // 19.0 of four; 450 M of 256 streams: 510 and 644)
+            const int least = L.dist == kNormal && L.q * L.S < kNarrowFrom ? 4 : 1;
             const ChunkChoice e = choose_chunks(n_sblk, units_max, w, most, L.block / 64, t.lock != 0,
-                                                shared, kUnitSlots[tuned_kind(L)], L.spl);
+                                                shared, least, kUnitSlots[tuned_kind(L)], L.spl);
             c = e.chunk;
             L.block = 64 * e.wpb;
             chosen = true;

@@ -114,14 +114,14 @@ def grid_cost(n_sblk, units, chunks, wpb, lock, kind, spl):
     return cost + (FINALIZE_US if k > 1 and not column else 0.0), chunk, k
 
 
-def choose_chunks(n_sblk, units, aim, most, wpb, lock, shared, kind, spl):
+def choose_chunks(n_sblk, units, aim, most, wpb, lock, shared, least, kind, spl):
     """(chunk, waves per block) of the grid that costs least around the aim."""
     cost, chunk, _ = grid_cost(n_sblk, units, aim, wpb, lock, kind, spl)
     best = cost, chunk, wpb
     w = wpb
     while w >= 1:
         whole = w >= n_sblk
-        if w < wpb and not whole and (shared or w < 4):
+        if w < wpb and (w < least if whole else shared or w < 4):
             break
         row = -(-n_sblk // w)
         handicap = 1.01 if w == wpb else 1.04
@@ -130,7 +130,7 @@ def choose_chunks(n_sblk, units, aim, most, wpb, lock, shared, kind, spl):
             ks = [256 * m // row for m in range(max(1, r - r // 3), min(r + r // 2 + (1 if shared else 3), r + 7) + 1)]
         else:
             ks = range(aim - aim // 3, aim + aim // 2 + (2 if shared else 6) + 1)
-        for k in ks:
+        for k in ([aim] if w < wpb else []) + list(ks):
             if 1 <= k <= most:
                 cost, chunk, _ = grid_cost(n_sblk, units, k, w, lock, kind, spl)
                 far = float(k) / float(aim)
@@ -176,7 +176,9 @@ def resolve(entry, S, n, dist, dtype):
     block, chunk = entry["block"], max(1, -(-units_max // w))
     chosen = n_sblk * w > ONE_WAVE
     if chosen:
-        chunk, wpb = choose_chunks(n_sblk, units_max, w, most, wide, entry["lock"], shared, kind_of(dist, dtype), spl)
+        least = 4 if dist == NORMAL and q * S < NARROW_FROM else 1
+        chunk, wpb = choose_chunks(n_sblk, units_max, w, most, wide, entry["lock"], shared, least,
+                                   kind_of(dist, dtype), spl)
         block = 64 * wpb
     nch = -(-units_max // chunk) if units_max else 0
     if nch > 65535:

@@ -52,3 +52,13 @@ def test_mostly_idle_last_blocks_get_many_chunks():
         plan = P.mrg_generate_plan(S, 1 << 28, P.MRG_UNIFORM, P.MRG_F32)
         chunks = -(-((1 << 28) // S + 1) // plan["chunk"])
         assert plan["lockstep"] and -(-S // 64) * chunks >= 16384, plan
+
+
+@pytest.mark.parametrize("dtype", [P.MRG_F64, P.MRG_F32])
+@pytest.mark.parametrize("S", [64, 77, 128])
+def test_short_normals_stage_their_tables_by_four_waves(S, dtype):
+    """Rows that fit in one block may take a block of one or two waves; calls of normals
+    too short to spread the staging of the tables keep four."""
+    for n in (1 << 22, 1 << 23, 1 << 24, (1 << 26) - 64):
+        plan = P.mrg_generate_plan(S, n // S * S, P.MRG_NORMAL, dtype)
+        assert plan["block"] >= 256, (n, plan)
