@@ -1157,7 +1157,7 @@ static ChunkChoice grid_cost(uint64_t n_sblk, uint64_t units, uint64_t chunks, i
 // keep their width, how much of a row a block writes whole, and few chunks; rows that
 // fit in one block keep `least` waves of it.  Rounding the aim up by itself leaves most
 // stream counts with a round of a few blocks: 2^28 fp32 uniforms of 20,032 streams (260
-// blocks of 4 waves) took 313 us, 222 with blocks that fill their rounds.
+// blocks of 4 waves) took 312 us, 213 with blocks that fill their rounds.
 static ChunkChoice choose_chunks(uint64_t n_sblk, uint64_t units, uint64_t aim, uint64_t most, int wpb, bool lock,
                                  bool shared, int least, double unit_slots, int spl) {
     ChunkChoice best = grid_cost(n_sblk, units, aim, wpb, lock, unit_slots, spl);
