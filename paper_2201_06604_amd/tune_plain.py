@@ -190,7 +190,7 @@ def resolve(entry, S, n, dist, dtype):
     column = not lock and 1 < nch <= wpb
     if not chosen and not lock and not column and n_sblk * nch < 2048 and block > 256:
         block, wpb = 256, 4
-    if column and n_sblk % 8:
+    if not lock and (n_sblk if column else -(-n_sblk // wpb) * nch) % 8:
         xcd = 0
     return {"block": block, "chunk": chunk, "nontemporal": 1 if (S * esz) % 128 == 0 else 0,
             "arith": 2, "streams_per_lane": spl, "xcd_remap": xcd, "lockstep": lock}
