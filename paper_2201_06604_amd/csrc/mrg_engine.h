@@ -260,26 +260,32 @@ __device__ __forceinline__ double2v* sincos_table_lds() {
     return tab;
 }
 
-// COUNT pairs from constant memory to LDS, one per lane, the block's waves in
-// turn.  The loop counter is wave-uniform (readfirstlane): a loop bounded by
+// COUNT pairs from constant memory to LDS (and their halves to `half`), one per
+// lane, the block's waves in turn.  The loop counter is wave-uniform (readfirstlane): a loop bounded by
 // threadIdx and blockDim themselves makes the compiler treat later row
 // addresses as divergent.
 template <int COUNT>
-__device__ __forceinline__ void stage_pairs(double2v* dst, const double (*src)[2]) {
+__device__ __forceinline__ void stage_pairs(double2v* dst, const double (*src)[2], double2v* half = nullptr) {
     const int lane = static_cast<int>(threadIdx.x & 63);
     const int first = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int waves = static_cast<int>(blockDim.x >> 6);
     for (int k = first; k < (COUNT + 63) / 64; k += waves) {
         const int i = lane + 64 * k;
-        if (i < COUNT) dst[i] = double2v{src[i][0], src[i][1]};
+        if (i < COUNT) {
+            const double2v v = {src[i][0], src[i][1]};
+            dst[i] = v;
+            if (half) half[i] = v * 0.5;
+        }
     }
 }
 
 enum { kStageExponential = 0, kStageNormalF32 = 1, kStageNormal = 2, kStageAll = 3 };
 template <int WHAT>
 __device__ __forceinline__ void stage_tables() {
-    if constexpr (WHAT == kStageExponential || WHAT == kStageAll) stage_pairs<kLogTabN>(log_table_lds<1>(), g_logtab_half.e);
-    if constexpr (WHAT >= kStageNormalF32) stage_pairs<kLogTabN>(log_table_lds<2>(), g_logtab.e);
+    if constexpr (WHAT == kStageExponential) stage_pairs<kLogTabN>(log_table_lds<1>(), g_logtab_half.e);
+    if constexpr (WHAT == kStageNormalF32 || WHAT == kStageNormal) stage_pairs<kLogTabN>(log_table_lds<2>(), g_logtab.e);
+    // one read for both: a second costs every block its latency again
+    if constexpr (WHAT == kStageAll) stage_pairs<kLogTabN>(log_table_lds<2>(), g_logtab.e, log_table_lds<1>());
     if constexpr (WHAT >= kStageNormalF32) stage_pairs<kSinCosTabN>(sincos_table_lds(), g_sincostab.hi);
     if constexpr (WHAT >= kStageNormal) stage_pairs<kSinCosTabN>(sincos_table_lds() + kSinCosTabN, g_sincostab.lo);
     __syncthreads();
